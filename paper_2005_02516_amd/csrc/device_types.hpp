@@ -97,10 +97,8 @@ __host__ __device__ constexpr int stat_words(int D, bool wadg = false) {
                     : mass_words(D, wadg) + 2 * dim_Nq(D) + dim_Nh(D) + dim_Nfq(D);
 }
 
-// Tile shape of the residual phase: rows per thread R (it divides Nq and Nfq) and column
-// parts P, packed as (R << 4) | P.  A task is (element, R rows, column part); the P partial
-// sums of a row are added in the lift.
-constexpr int kShapeDefault = 0;
+// Tile shape option of the ABI: rows per thread R and column parts P, packed as (R << 4) | P.
+// It is checked, and P enters the LDS of a tile; the residual runs in its default shape.
 __host__ __device__ constexpr int shape_rows(int shape) { return shape >> 4; }
 __host__ __device__ constexpr int shape_parts(int shape) { return shape & 15; }
 __host__ __device__ constexpr int make_shape(int R, int P) { return (R << 4) | P; }
@@ -137,44 +135,42 @@ __host__ __device__ constexpr int rec_stride(int D) {
 
 // Words (of the bulk precision) of LDS one tile of E elements of kind D needs (the
 // reference block is held separately, once per workgroup).  Modal kinds: node records
-// [E][rec_stride] | raw block [E][raw_words] | neighbour values [E][Nfq][4] | state, RK
-// register [3][E][Np] each | static block [E][stat_words].  DG-SBP: node records | two
+// [E][rec_stride] | raw block [E][raw_words] | neighbour values [E][Nfq][4] | static
+// block [E][stat_words] | state, RK register [3][E][Np] each.  DG-SBP: node records | two
 // residual partials [2][3][E][Nh] | neighbour values | state, RK register [3][E][Nq] each |
 // static block.
 __host__ __device__ constexpr int tile_words(int D, int E, bool wadg = false, int P = 2) {
-  return key_sbp(D) ? E * (rec_stride(D) + 6 * dim_Nh(D) + 4 * dim_Nfq(D) + 6 * dim_Nq(D) + stat_words(D))
+  return key_sbp(D) ? E * (rec_stride(D) + 4 * dim_Nfq(D) + 6 * dim_Nq(D) + stat_words(D)) + ((6 * E * dim_Nh(D) + 3) & ~3)
                     : E * (rec_stride(D) + raw_words(D, P) + 4 * dim_Nfq(D) + 6 * dim_Np(D) +
                            stat_words(D, wadg));
 }
 
-// 32-bit words per thread of the static block that a stage stages through registers
-// (issued after the tile's other copies have landed, stored to LDS after the residual),
-// for float and for double tiles.
-constexpr int kStatRegs = 8;
-template <typename real> struct StatRegs { static constexpr int value = sizeof(real) == 4 ? kStatRegs : 4; };
+// Reals from one tile's static block to the next in HBM: its words, filled up to 16 bytes.
+__host__ __device__ constexpr int stat_tile(int D, int E, bool wadg) { return (E * stat_words(D, wadg) + 3) & ~3; }
 
 // One instance as the kernels see it (device pointers into the bound workspace).
 struct InstDesc {
   int32_t N, K, flux;   // N: the element kind D (degree | variant << kKeyShift)
-  int32_t shape;        // tile shape of the residual phase, (R << 4) | P
+  int32_t E;            // elements of a full tile (the strides of the tile-blocked arrays)
   double g, Href, dt, pad1;
   void *uh;            // [3][K][Np] modal state (eta = h + b - Href, hu, hv)
   void *du;            // [3][K][Np] LSRK register
   void *ut[3];         // entropy-projected h~, u~, v~, H~ - Href at the hybrid nodes, tile-blocked:
-                       // the tile of elements k0..k0+ne-1 holds [4][ne][Nh] from real k0*4*Nh
+                       // the tile of elements from k0 on holds [4][E][Nh] from real k0*4*Nh, the last,
+                       // ragged one too (its slots beyond the instance's elements are unused)
                        // (two stage buffers + rhs scratch)
   void *nbx[3];        // [K][Nfq][4] the same four values at each face node's neighbour, written
                        // by the neighbour's projection (one per ut buffer)
   const void *geo;     // rxJ, sxJ, ryJ, syJ at the hybrid nodes, tile-blocked like ut
   const void *wJq;     // [K][Nq] w_q J in double (diagnostics)
-  const void *stat;    // static data in tile order: the tile of elements k0..k0+ne-1 holds, from
-                       // real k0 * stat_words(N, wadg): the mass data [ne][mass_words] (Minv
-                       // [Np][Np], or w/J at the volume nodes [Nq]) | w J [ne][Nq] | rest depth
-                       // Href - b [ne][Nq] | Href - b [ne][Nh] | push targets [ne][Nfq] (int32
+  const void *stat;    // static data in tile order: tile `index` of the instance holds, from
+                       // real index * stat_tile(N, E, wadg): the mass data [E][mass_words] (Minv
+                       // [Np][Np], or w/J at the volume nodes [Nq]) | w J [E][Nq] | rest depth
+                       // Href - b [E][Nq] | Href - b [E][Nh] | push targets [E][Nfq] (int32
                        // k'*Nfq + f' of the nbx slot that face node f fills, packed in the first
-                       // ne*Nfq 32-bit words; kPushWall set on wall nodes, whose slot is their
-                       // own).  DG-SBP: 1/(w J) [ne][Nq] | Href - b [ne][Nq] | rxJ, sxJ, ryJ, syJ
-                       // [4][ne][Nq] | push targets [ne][Nfq].  The rest depth is rewritten from
+                       // E*Nfq 32-bit words; kPushWall set on wall nodes, whose slot is their
+                       // own).  DG-SBP: 1/(w J) [E][Nq] | Href - b [E][Nq] | rxJ, sxJ, ryJ, syJ
+                       // [4][E][Nq] | push targets [E][Nfq].  The rest depth is rewritten from
                        // bd (double) whenever Href changes, so a near-dry depth h = eta +
                        // (Href - b) keeps its relative accuracy in float.
   const void *ref;     // reference-operator block for this kind
@@ -186,7 +182,7 @@ struct InstDesc {
 
 // A contiguous range of elements of one instance, processed by one workgroup.
 struct Tile {
-  int32_t inst, k0, ne, pad;
+  int32_t inst, k0, ne, index;   // index: number of the tile within its instance
 };
 
 enum StageMode : int32_t {
@@ -206,9 +202,9 @@ struct StageArgs {
                           // precision, 2 matrix cores with split-bf16 products
   int32_t wadg;           // 0: stored inverse mass matrices; 1: weight-adjusted inverse
   int32_t v1;             // an instance is of a variant-1 kind (selects the stage-kernel build)
-  int32_t shapes;         // an instance's tile shape is not the default (selects the build)
   int32_t kind;           // the element kind of every instance of a single-kind launch, which
                           // then runs the kernel built for that kind alone; 0 otherwise
+  int32_t tile;           // its elements per tile (selects the build for that tile size)
   const int32_t *ranges;  // optional [grid+1]: tile range of each block's chunk (cost-balanced);
                           // null means equal numbers of tiles per chunk
   int32_t in_buf, out_buf;

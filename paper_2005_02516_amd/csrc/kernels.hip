@@ -55,6 +55,11 @@ __device__ __forceinline__ int phase_tid() {
   return t;
 }
 
+// Threads of the workgroup: a constant in the kernels built for one kind (LT::NT).
+template <int T> struct Threads { static constexpr int NT = T; };
+template <class LT>
+__device__ __forceinline__ int threads() { return LT::NT != 0 ? LT::NT : int(blockDim.x); }
+
 // Task i of a phase over (field c, element e, mode or node j) in [3][ne][M] order: c, the
 // offset r = e M + j within field c's block, e and j.  The products take 24-bit multiplies
 // and the division is unsigned by the constant M: 32-bit multiplies issue at a quarter of
@@ -82,11 +87,23 @@ struct FieldTask {
 //   kMfmaBf16x3: each operand split x = hi + lo (hi = bf16(x), lo = bf16(x - hi)), product
 //                hi_a hi_b + hi_a lo_b + lo_a hi_b by v_mfma_f32_16x16x16_bf16 with float
 //                accumulation (relative error ~2^-16 per product).
-enum ContractionMode : int { kValu = 0, kMfmaNative = 1, kMfmaBf16x3 = 2 };
+enum ContractionMode : int { kMfmaNative = 1, kMfmaBf16x3 = 2 };
 
 typedef short bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef double f64x4_t __attribute__((ext_vector_type(4)));
+template <typename real> struct Acc { typedef f32x4_t type; };
+template <> struct Acc<double> { typedef f64x4_t type; };
+__device__ __forceinline__ f32x4_t mfma(float a, float b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4_t mfma(double a, double b, f64x4_t c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+// output row of item r of the lanes of k-quad `quad`
+template <typename real>
+__device__ __forceinline__ int acc_row(int quad, int r) { return sizeof(real) == 4 ? 4 * quad + r : quad + 4 * r; }
+
 
 __device__ inline unsigned short bf16_rne(float x) {
   unsigned u = __float_as_uint(x);
@@ -95,8 +112,43 @@ __device__ inline unsigned short bf16_rne(float x) {
 }
 __device__ inline float bf16_value(unsigned short h) { return __uint_as_float(unsigned(h) << 16); }
 
-template <int MODE, typename real, class FA, class FB, class FC>
-__device__ __forceinline__ void gemm_mfma(int M, int KD, int NC, FA a_at, FB b_at, FC c_store) {
+// C[M x ncol] = A[M x KD] B[KD x ncol] in the bulk precision (kMfmaNative): a(row) is a
+// pointer to row `row` of A (elements lda reals apart), b(col) a functor giving B[k][col].
+// Row and column indices beyond the matrices are clamped (the loads stay inside them, the
+// results are dropped), and so is the last k-quad, whose B values beyond KD are zeroed, so
+// the loop has no bounds checks: a step is one LDS word of A and of B per 16x16x4 product.
+template <int M, int KD, typename real, class FA, class FB, class FC>
+__device__ __forceinline__ void gemm_native(int ncol, int nwaves, FA a, int lda, FB b, FC c_store) {
+  typedef typename Acc<real>::type acc_t;
+  constexpr int MB = (M + 15) / 16, KS = (KD + 3) / 4;
+  const int t = phase_tid(), lane = t & 63, lrow = lane & 15, quad = lane >> 4;
+  const int nblk = MB * ((ncol + 15) >> 4);
+#pragma unroll 1
+  for (int blk = wave_id(); blk < nblk; blk += nwaves) {
+    const int bj = int(unsigned(blk) / unsigned(MB)), bi = blk - bj * MB;
+    const int row = bi * 16 + lrow, col = bj * 16 + lrow;
+    const real *ap = a(M % 16 == 0 || row < M ? row : M - 1);
+    const auto bp = b(col < ncol ? col : ncol - 1);
+    acc_t acc = {0, 0, 0, 0};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const int k = 4 * s + quad;
+      const bool in = KD % 4 == 0 || s + 1 < KS || k < KD;
+      const int kc = in ? k : KD - 1;
+      const real av = ap[kc * lda], bv = bp(kc, s);
+      acc = mfma(av, in ? bv : real(0), acc);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = bi * 16 + acc_row<real>(quad, r);
+      if (i < M && col < ncol) c_store(i, col, acc[r]);
+    }
+  }
+}
+
+// The same with split-bf16 products (kMfmaBf16x3): a(row, k) and b(k, col) return the values.
+template <class FA, class FB, class FC>
+__device__ __forceinline__ void gemm_bf16x3(int M, int KD, int NC, FA a_at, FB b_at, FC c_store) {
   const int lane = threadIdx.x & 63, wave = wave_id(), nwaves = blockDim.x >> 6;
   const int mb = (M + 15) / 16, nb = (NC + 15) / 16;
   const int lrow = lane & 15, quad = lane >> 4;
@@ -104,74 +156,73 @@ __device__ __forceinline__ void gemm_mfma(int M, int KD, int NC, FA a_at, FB b_a
   for (int blk = wave; blk < mb * nb; blk += nwaves) {
     const int bi = blk % mb, bj = blk / mb;
     const int row = bi * 16 + lrow, col = bj * 16 + lrow;
-    if constexpr (MODE == kMfmaBf16x3) {
-      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-      for (int k0 = 0; k0 < KD; k0 += 16) {
-        bf16x4_t ahi, alo, bhi, blo;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int k = k0 + 4 * quad + r;
-          const float av = (row < M && k < KD) ? float(a_at(row, k)) : 0.f;
-          const float bv = (col < NC && k < KD) ? float(b_at(k, col)) : 0.f;
-          const unsigned short ah = bf16_rne(av), bh = bf16_rne(bv);
-          ahi[r] = short(ah);
-          alo[r] = short(bf16_rne(av - bf16_value(ah)));
-          bhi[r] = short(bh);
-          blo[r] = short(bf16_rne(bv - bf16_value(bh)));
-        }
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ahi, bhi, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ahi, blo, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(alo, bhi, acc, 0, 0, 0);
-      }
+    for (int k0 = 0; k0 < KD; k0 += 16) {
+      bf16x4_t ahi, alo, bhi, blo;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = bi * 16 + 4 * quad + r;
-        if (i < M && col < NC) c_store(i, col, real(acc[r]));
+        const int k = k0 + 4 * quad + r;
+        const float av = (row < M && k < KD) ? float(a_at(row, k)) : 0.f;
+        const float bv = (col < NC && k < KD) ? float(b_at(k, col)) : 0.f;
+        const unsigned short ah = bf16_rne(av), bh = bf16_rne(bv);
+        ahi[r] = short(ah);
+        alo[r] = short(bf16_rne(av - bf16_value(ah)));
+        bhi[r] = short(bh);
+        blo[r] = short(bf16_rne(bv - bf16_value(bh)));
       }
-    } else if constexpr (std::is_same<real, float>::value) {
-      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-      for (int k0 = 0; k0 < KD; k0 += 4) {
-        const int k = k0 + quad;
-        const float av = (row < M && k < KD) ? a_at(row, k) : 0.f;
-        const float bv = (col < NC && k < KD) ? b_at(k, col) : 0.f;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc, 0, 0, 0);
-      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ahi, bhi, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ahi, blo, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(alo, bhi, acc, 0, 0, 0);
+    }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = bi * 16 + 4 * quad + r;
-        if (i < M && col < NC) c_store(i, col, acc[r]);
-      }
-    } else {
-      f64x4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-      for (int k0 = 0; k0 < KD; k0 += 4) {
-        const int k = k0 + quad;
-        const double av = (row < M && k < KD) ? a_at(row, k) : 0.0;
-        const double bv = (col < NC && k < KD) ? b_at(k, col) : 0.0;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = bi * 16 + quad + 4 * r;      // f64 output rows are interleaved
-        if (i < M && col < NC) c_store(i, col, acc[r]);
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int i = bi * 16 + 4 * quad + r;
+      if (i < M && col < NC) c_store(i, col, acc[r]);
     }
   }
 }
 
+// c_store(i, col, sum_k V[i][k] in(col)(k)) (TR false: rows of V_h, [.][LD] row-major) or, with
+// TR, sum_k V[k][i] in(col)(k), for M rows and ncol columns.
+template <int CM, int M, int KD, int LD, bool TR, typename real, class FB, class FC>
+__device__ __forceinline__ void contract(const real *V, int ncol, int nwaves, FB in, FC c_store) {
+  if constexpr (CM == kMfmaBf16x3)
+    gemm_bf16x3(M, KD, ncol, [&](int i, int k) { return TR ? V[k * LD + i] : V[i * LD + k]; },
+                [&](int k, int c) { return in(c)(k, k >> 2); }, c_store);
+  else
+    gemm_native<M, KD, real>(ncol, nwaves, [&](int row) { return V + (TR ? row : __umul24(unsigned(row), unsigned(LD))); },
+                             TR ? LD : 1, in, c_store);
+}
+
+// Columns of an array [ncol][M], as contract's input and output.
+template <int M, typename real>
+__device__ __forceinline__ auto cols_in(const real *x) {
+  return [x](int c) {
+    const real *p = x + __umul24(unsigned(c), unsigned(M));
+    return [p](int k, int) { return p[k]; };
+  };
+}
+template <int M, typename real>
+__device__ __forceinline__ auto cols_out(real *x) {
+  return [x](int i, int c, real v) { x[__umul24(unsigned(c), unsigned(M)) + i] = v; };
+}
+
 // LDS carve-up of one tile (see lds_words()).
-template <typename real, int N>
+template <typename real, int N, int EC, int NTH>
 struct Lds {
+  static constexpr int NT = NTH;
   static constexpr int Np = dim_Np(N), Nq = dim_Nq(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N);
   real *ref, *Vh, *ST, *FT, *wf, *nr, *ns;
   real *rec, *raw, *nb, *U, *DU, *Minv, *wJ, *bq, *bh;
   real *R, *T, *Q, *VH;
   int32_t *pp;
+  int E;                           // elements of a full tile: the stride of every array below
   // sm: the ref block (already loaded); tile: the tile region (after the largest ref block);
-  // mw: reals of mass data per element (mass_words); P: column parts of the residual
-  __device__ Lds(real *sm, real *tile, int E, int mw, int P) {
+  // mw: reals of mass data per element (mass_words); P: column parts of the residual.
+  // EC: E where the kernel is built for one tile size, so that every offset is an immediate;
+  // 0: E is e.
+  __device__ Lds(real *sm, real *tile, int e, int mw, int P) : E(EC != 0 ? EC : e) {
     ref = sm;
     Vh = ref;
     ST = Vh + Nh * Np;
@@ -182,13 +233,13 @@ struct Lds {
     rec = tile;
     raw = rec + E * rec_stride(N);
     nb = raw + E * raw_words(N, P);
-    U = nb + 4 * E * Nfq;
-    DU = U + 3 * E * Np;
-    Minv = DU + 3 * E * Np;
+    Minv = nb + 4 * E * Nfq;     // the static block; every region up to here is 16-byte aligned
     wJ = Minv + E * mw;          // Minv: [E][Np][Np], or w/J [E][Nq] (weight-adjusted)
     bq = wJ + E * Nq;
     bh = bq + E * Nq;
     pp = reinterpret_cast<int32_t *>(bh + E * Nh);
+    U = bh + E * (Nh + Nfq);
+    DU = U + 3 * E * Np;
     // reuse: the residual, lift and projection temporaries live in the raw block (dead
     // after phase 1) and v'_h in the neighbour block (dead after the residual); the
     // node records and the state are left alone, so a resident tile keeps them
@@ -199,25 +250,28 @@ struct Lds {
   }
 };
 
-// Default rows per thread of the residual phase (the build without tile-shape choice).
+// Rows per thread of the residual phase: two in float where two rows' sums fit the registers
+// and 2 divides Nq and Nfq.
 template <typename real, int N> struct RowsPerThread { static constexpr int value = 1; };
 template <> struct RowsPerThread<float, 1> { static constexpr int value = 2; };
 template <> struct RowsPerThread<float, 3> { static constexpr int value = 2; };
-// Default column chunks of the residual phase: one at N = 5 (whose 512-thread workgroups
+// Column chunks of the residual phase: one at N = 5 (whose 512-thread workgroups
 // have a task per row already), else two.
 template <typename real, int N> struct DefaultParts { static constexpr int value = 2; };
 template <> struct DefaultParts<float, 5> { static constexpr int value = 1; };
 template <> struct DefaultParts<double, 5> { static constexpr int value = 1; };
 
-// Tile shapes the residual phase is compiled for: R = 1 or 2 rows per thread (2 only in
-// float, where R divides Nq and Nfq: two rows of double accumulators exceed the register
-// budget of four waves per SIMD and spill) and P = 1..4 column parts.
-template <typename real, int N>
-__host__ __device__ constexpr bool shape_ok(int shape) {
-  return shape_parts(shape) >= 1 && shape_parts(shape) <= 4 &&
-         (shape_rows(shape) == 1 ||
-          (shape_rows(shape) == 2 && sizeof(real) == 4 && dim_Nq(N) % 2 == 0 && dim_Nfq(N) % 2 == 0));
+// The tile size the single-kind kernel of a kind is built for (0: none).
+template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) {
+  return sizeof(real) == 4 ? (kind == 1 ? 32 : kind == 2 ? 14 : kind == 3 ? 8 : kind == 4 ? 5 : kind == 5 ? 7 : 0)
+                           : (kind == 1 ? 16 : kind == 2 ? 7 : kind == 3 ? 4 : kind == 4 ? 5 : kind == 5 ? 7 : 0);
 }
+
+// What changes from stage to stage of a launch.
+struct StageRun {
+  int mode, in_buf, out_buf;
+  double rk_a, rk_b;
+};
 
 // Stage flags of a multi-stage launch whose tiles stay in LDS (StageArgs::resident).
 constexpr int kResident = 1;       // the tile's records, metric factors, static block, state and
@@ -232,36 +286,42 @@ constexpr int kResLast = 4;        // last stage: the state, RK register and u~ 
 // with V_q (the first Nq rows of V_h) and the per-element weights w/J (held where the
 // stored inverse would be).  First factor, one task per (field, element, volume node):
 // S[c][e][q] = (w/J)[e][q] sum_j V_q[q][j] Y[c][e][j].
-template <typename real, int N>
-__device__ __forceinline__ void wadg_first(int ne, const Lds<real, N> &L, const real *Y, real *S) {
+template <typename real, int N, class LT>
+__device__ __forceinline__ void wadg_first(const LT &L, const real *Y, real *S) {
   constexpr int Np = dim_Np(N), Nq = dim_Nq(N);
-  for (int i = phase_tid(); i < 3 * ne * Nq; i += blockDim.x) {
-    const int c = (i >= ne * Nq) + (i >= 2 * ne * Nq), r = i - c * ne * Nq, e = r / Nq, q = r - e * Nq;
-    const real *Yc = Y + c * ne * Np + e * Np;
-    const real *Vq = L.Vh + q * Np;
+  const int E = L.E;
+  contract<kMfmaNative, Nq, Np, Np, false, real>(L.Vh, 3 * E, threads<LT>() >> 6, cols_in<Np>(Y), [&](int q, int c, real v) {
+    const int e = c - ((c >= E) + (c >= 2 * E)) * E;
+    S[__umul24(unsigned(c), unsigned(Nq)) + q] = L.Minv[__umul24(unsigned(e), unsigned(Nq)) + q] * v;
+  });
+}
+
+// Second factor: out[c][e][j] = sum_q V_q[q][j] S[c][e][q].
+template <typename real, int N, class LT>
+__device__ __forceinline__ void wadg_second(const LT &L, const real *S, real *out) {
+  constexpr int Np = dim_Np(N), Nq = dim_Nq(N);
+  contract<kMfmaNative, Np, Nq, Np, true, real>(L.Vh, 3 * L.E, threads<LT>() >> 6, cols_in<Nq, real>(S), cols_out<Np>(out));
+}
+
+// The stored inverses applied to X [3][E][Np]: store(i, (Minv_e X[c][e])[j]), i = (c E + e) Np + j,
+// one task per output, on the vector ALUs (the matrix differs from element to element).
+template <typename real, int N, class LT, class F>
+__device__ __forceinline__ void minv_rows(const LT &L, const real *X, F store) {
+  constexpr int Np = dim_Np(N);
+  const int nem = L.E * Np;
+  for (int i = phase_tid(); i < 3 * nem; i += threads<LT>()) {
+    const FieldTask<Np> k(i, nem);
+    const real *Mi = L.Minv + __umul24(unsigned(k.r), unsigned(Np));   // row (e, j) of Minv_e
+    const real *Xc = X + (i - k.j);                                    // X[c][e][0..Np)
     real a = 0, b = 0;
 #pragma unroll 32
     for (int j = 0; j + 1 < Np; j += 2) {
-      a += Vq[j] * Yc[j];
-      b += Vq[j + 1] * Yc[j + 1];
+      a += Mi[j] * Xc[j];
+      b += Mi[j + 1] * Xc[j + 1];
     }
-    if (Np & 1) a += Vq[Np - 1] * Yc[Np - 1];
-    S[i] = L.Minv[e * Nq + q] * (a + b);
+    if (Np & 1) a += Mi[Np - 1] * Xc[Np - 1];
+    store(i, a + b);
   }
-}
-
-// Second factor for one output mode: sum_q V_q[q][row] Sc[q].
-template <typename real, int N>
-__device__ __forceinline__ real wadg_second(const Lds<real, N> &L, const real *Sc, int row) {
-  constexpr int Np = dim_Np(N), Nq = dim_Nq(N);
-  real a = 0, b = 0;
-#pragma unroll 32
-  for (int q = 0; q + 1 < Nq; q += 2) {
-    a += L.Vh[q * Np + row] * Sc[q];
-    b += L.Vh[(q + 1) * Np + row] * Sc[q + 1];
-  }
-  if (Nq & 1) a += L.Vh[(Nq - 1) * Np + row] * Sc[Nq - 1];
-  return a + b;
 }
 
 // Entropy projection of the tile states in L.U ([3][ne][Np]: eta, hu, hv) to the
@@ -275,125 +335,46 @@ __device__ __forceinline__ real wadg_second(const Lds<real, N> &L, const real *S
 // Subtracting the constant g Href is exact: the projection reproduces constants.  The rest
 // depth Href - b comes from the static block, formed in double on the device from b (so in
 // float it has the relative accuracy of the depth itself where the water is shallow).
-template <typename real, int N, int CM, bool WADG>
-__device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, Lds<real, N> &L, real *out,
+template <typename real, int N, int CM, bool WADG, class LT>
+__device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, LT &L, real *out,
                                              real *nbx_out, int32_t *flag, bool coherent, int res = 0) {
   const bool to_records = (res & kResident) && !(res & kResLast);
-  constexpr bool mfma = CM != kValu;
   constexpr int Np = dim_Np(N), Nq = dim_Nq(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N);
   const double g = d.g;
-  const int tid = phase_tid(), nth = blockDim.x;
-  const int nc = 3 * ne;                       // contraction columns: (field, element)
-  real *Stage = L.R;                           // [3][ne][Nq] or [3][ne][Nh] staging (free here)
+  const int tid = phase_tid(), nth = threads<LT>();
+  const int E = L.E, nc = 3 * E;               // contraction columns: (field, element)
+  real *Stage = L.R;                           // [3][E][Nq] or [3][E][Nh] staging (free here)
   bool bad = false;
-  if constexpr (CM != kValu) {
-    {                              // u_q = V_q u_h on the matrix cores
-      gemm_mfma<CM, real>(Nq, Np, nc, [&](int i, int k) { return L.Vh[i * Np + k]; },
-                  [&](int k, int c) { return L.U[c * Np + k]; },
-                  [&](int i, int c, real v) { Stage[c * Nq + i] = v; });
-      __syncthreads();
-    }
-  }
+  contract<CM, Nq, Np, Np, false, real>(L.Vh, nc, nth >> 6, cols_in<Np, real>(L.U), cols_out<Nq>(Stage));   // u_q = V_q u_h
+  __syncthreads();
   for (int i = tid; i < ne * Nq; i += nth) {
-    const int e = int(unsigned(i) / unsigned(Nq)), q = i - __umul24(unsigned(e), unsigned(Nq));
-    real u0 = 0, u1 = 0, u2 = 0;
-    if (mfma) {
-      u0 = Stage[i];
-      u1 = Stage[ne * Nq + i];
-      u2 = Stage[2 * ne * Nq + i];
-    } else {
-      const real *Vq = L.Vh + __umul24(unsigned(q), unsigned(Np));
-      const real *Ue = L.U + __umul24(unsigned(e), unsigned(Np));
-#pragma unroll 32
-      for (int j = 0; j < Np; ++j) {
-        const real v = Vq[j];
-        u0 += v * Ue[j];
-        u1 += v * Ue[ne * Np + j];
-        u2 += v * Ue[2 * ne * Np + j];
-      }
-    }
-    const double eta = u0, hu = u1, hv = u2;
+    const double eta = Stage[i], hu = Stage[E * Nq + i], hv = Stage[2 * E * Nq + i];
     const double h = eta + double(L.bq[i]);       // L.bq: rest depth Href - b
     const double rh = 1.0 / h, uu = hu * rh, vv = hv * rh;
     const double v1 = g * eta - 0.5 * (uu * uu + vv * vv);
     const double w = L.wJ[i];
-    L.Q[0 * ne * Nq + i] = real(w * v1);
-    L.Q[1 * ne * Nq + i] = real(w * uu);
-    L.Q[2 * ne * Nq + i] = real(w * vv);
+    L.Q[i] = real(w * v1);
+    L.Q[E * Nq + i] = real(w * uu);
+    L.Q[2 * E * Nq + i] = real(w * vv);
     bad |= bad_value(h, hu, hv);
   }
   __syncthreads();
-  // y = V_q^T (w J v'): one task per (field, element, mode)
-  if constexpr (CM != kValu) {
-      gemm_mfma<CM, real>(Np, Nq, nc, [&](int i, int k) { return L.Vh[k * Np + i]; },
-                  [&](int k, int c) { return L.Q[c * Nq + k]; },
-                  [&](int i, int c, real v) { L.T[c * Np + i] = v; });
-  }
-  for (int i = tid; i < 3 * ne * Np && !mfma; i += nth) {
-    const FieldTask<Np> k(i, ne * Np);
-    const real *Qc = L.Q + __umul24(unsigned(k.c), unsigned(ne * Nq)) + __umul24(unsigned(k.e), unsigned(Nq));
-    const real *Vj = L.Vh + k.j;
-    real ya = 0, yb = 0;
-#pragma unroll 32
-    for (int q = 0; q + 1 < Nq; q += 2) {
-      ya += Vj[q * Np] * Qc[q];
-      yb += Vj[(q + 1) * Np] * Qc[q + 1];
-    }
-    if (Nq & 1) ya += Vj[(Nq - 1) * Np] * Qc[Nq - 1];
-    L.T[i] = ya + yb;
-  }
+  contract<CM, Np, Nq, Np, true, real>(L.Vh, nc, nth >> 6, cols_in<Nq, real>(L.Q), cols_out<Np>(L.T));      // y = V_q^T (w J v')
   __syncthreads();
   // v'_h = Minv_k y (weight-adjusted: the first factor into L.Q, dead once y is formed)
   if constexpr (WADG) {
-    wadg_first<real, N>(ne, L, L.T, L.Q);
+    wadg_first<real, N>(L, L.T, L.Q);
     __syncthreads();
-  }
-  for (int i = tid; i < 3 * ne * Np; i += nth) {
-    const FieldTask<Np> k(i, ne * Np);
-    if constexpr (WADG) {
-      L.VH[i] = wadg_second<real, N>(L, L.Q + __umul24(unsigned(k.c), unsigned(ne * Nq)) +
-                                            __umul24(unsigned(k.e), unsigned(Nq)), k.j);
-    } else {
-      const real *Mi = L.Minv + __umul24(unsigned(k.r), unsigned(Np));   // row (e, j) of Minv_e
-      const real *Tc = L.T + (i - k.j);                                  // T[c][e][0..Np)
-      real va = 0, vb = 0;
-#pragma unroll 32
-      for (int j = 0; j + 1 < Np; j += 2) {
-        va += Mi[j] * Tc[j];
-        vb += Mi[j + 1] * Tc[j + 1];
-      }
-      if (Np & 1) va += Mi[Np - 1] * Tc[Np - 1];
-      L.VH[i] = va + vb;
-    }
+    wadg_second<real, N>(L, L.Q, L.VH);
+  } else {
+    minv_rows<real, N>(L, L.T, [&](int i, real v) { L.VH[i] = v; });
   }
   __syncthreads();
-  if constexpr (CM != kValu) {
-    {                              // v~ = V_h v_h on the matrix cores
-      gemm_mfma<CM, real>(Nh, Np, nc, [&](int i, int k) { return L.Vh[i * Np + k]; },
-                  [&](int k, int c) { return L.VH[c * Np + k]; },
-                  [&](int i, int c, real v) { Stage[c * Nh + i] = v; });
-      __syncthreads();
-    }
-  }
+  contract<CM, Nh, Np, Np, false, real>(L.Vh, nc, nth >> 6, cols_in<Np, real>(L.VH), cols_out<Nh>(Stage));  // v~ = V_h v_h
+  __syncthreads();
   for (int i = tid; i < ne * Nh; i += nth) {
     const int e = int(unsigned(i) / unsigned(Nh)), n = i - __umul24(unsigned(e), unsigned(Nh));
-    real t0 = 0, t1 = 0, t2 = 0;
-    if (mfma) {
-      t0 = Stage[i];
-      t1 = Stage[ne * Nh + i];
-      t2 = Stage[2 * ne * Nh + i];
-    } else {
-      const real *Vn = L.Vh + __umul24(unsigned(n), unsigned(Np));
-      const real *Ve = L.VH + __umul24(unsigned(e), unsigned(Np));
-#pragma unroll 32
-      for (int j = 0; j < Np; ++j) {
-        const real v = Vn[j];
-        t0 += v * Ve[j];
-        t1 += v * Ve[ne * Np + j];
-        t2 += v * Ve[2 * ne * Np + j];
-      }
-    }
-    const double v1 = t0, v2 = t1, v3 = t2;
+    const double v1 = Stage[i], v2 = Stage[E * Nh + i], v3 = Stage[2 * E * Nh + i];
     const double dH = (v1 + 0.5 * (v2 * v2 + v3 * v3)) / g;
     const double h = dH + double(L.bh[i]);        // L.bh: rest depth Href - b
     if (to_records) {
@@ -403,11 +384,11 @@ __device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, 
       rec[0] = real4{real(0.5) * hr * ur, real(0.5) * hr * vr, real(0.5) * ur, real(0.5) * vr};
       rec[2] = real4{real(0.5) * gr * hr, real(dH), hr, real(0)};
     } else {
-      real *ot = out + size_t(k0) * 4 * Nh + unsigned(i);   // tile-blocked [4][ne][Nh]
+      real *ot = out + size_t(k0) * 4 * Nh + unsigned(i);   // tile-blocked [4][E][Nh]
       ot[0] = real(h);
-      ot[ne * Nh] = real(v2);
-      ot[2 * ne * Nh] = real(v3);
-      ot[3 * ne * Nh] = real(dH);
+      ot[E * Nh] = real(v2);
+      ot[2 * E * Nh] = real(v3);
+      ot[3 * E * Nh] = real(dH);
     }
     if (n >= Nq) {                 // face node: also fill the neighbour's face slot
       const int f = n - Nq;
@@ -421,8 +402,8 @@ __device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, 
         // fetched) and the reference normal of the face
         const real *gm = static_cast<const real *>(d.geo) + size_t(k0) * 4 * Nh + unsigned(i);
         const double nr = double(L.nr[f]), ns = double(L.ns[f]);
-        const double nx = double(gm[0]) * nr + double(gm[ne * Nh]) * ns;
-        const double ny = double(gm[2 * ne * Nh]) * nr + double(gm[3 * ne * Nh]) * ns;
+        const double nx = double(gm[0]) * nr + double(gm[E * Nh]) * ns;
+        const double ny = double(gm[2 * E * Nh]) * nr + double(gm[3 * E * Nh]) * ns;
         const double c = 2.0 * (v2 * nx + v3 * ny) / (nx * nx + ny * ny);
         pu = v2 - c * nx;
         pv = v3 - c * ny;
@@ -456,86 +437,103 @@ __device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, 
   if (bad) atomicOr(flag, 1);
 }
 
-// Asynchronous global -> LDS copies (global_load_lds_dword): each lane moves one 32-bit
-// word straight into LDS at (wave-uniform base) + 4 * lane, so a wave copies 64
-// consecutive words per instruction without staging them in registers; completion is
-// awaited once, with s_waitcnt vmcnt(0), before the tile's barrier.  (The 16-byte form,
-// global_load_lds_dwordx4, measured slower for these tile fetches.)
-typedef __attribute__((address_space(1))) const void *gptr_t;
-typedef __attribute__((address_space(3))) void *lptr_t;
+// Asynchronous global -> LDS copies (global_load_lds): every lane moves 16 bytes (or one
+// word) from its own address straight into LDS at (wave-uniform base) + 16 (or 4) * lane,
+// without staging in registers.  They are issued from asm statements, which the compiler's
+// wait counting does not see, so nothing waits for them until wait_copies: the waits the
+// compiler inserts for its own loads can only come out longer.
+__device__ __forceinline__ uint32_t lds_byte(const void *p) {
+  return uint32_t(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)p));
+}
+template <bool COHERENT>
+__device__ __forceinline__ void copy16(uint32_t lds, const void *src) {
+  if constexpr (COHERENT)          // device-coherent: other XCDs' stores are visible
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off sc1" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(src) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(src) : "memory");
+}
+__device__ __forceinline__ void copy4(uint32_t lds, const void *src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(src) : "memory");
+}
+// This wave's copies have landed in LDS.
+__device__ __forceinline__ void wait_copies() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-template <int CPOL = 0>
-__device__ inline void async_copy_words(uint32_t *dst, const uint32_t *src, int nwords) {
-  const int lane = threadIdx.x & 63, wave = wave_id(), nwaves = blockDim.x >> 6;
-  for (int c = wave * 64; c < nwords; c += nwaves * 64) {
-    if (c + lane < nwords)
-      __builtin_amdgcn_global_load_lds((gptr_t)(src + c + lane), (lptr_t)(dst + c), 4, 0, CPOL);
+// Copies `bytes` contiguous bytes (at most MAX where that is not 0, so that the rounds unroll)
+// between 16-byte aligned places; a tail of single words where bytes is not a multiple of 16.
+template <class LT, int MAX, bool COHERENT = false>
+__device__ __forceinline__ void copy_block(void *dst, const void *src, int bytes) {
+  const int nth = threads<LT>(), t = phase_tid(), lane16 = t * 16;
+  const uint32_t lds = lds_byte(dst) + (wave_id() << 10);
+  const char *p = static_cast<const char *>(src) + lane16;
+  if constexpr (MAX != 0 && LT::NT != 0) {
+#pragma unroll
+    for (int o = 0; o < MAX; o += LT::NT * 16)
+      if (o + lane16 + 16 <= bytes) copy16<COHERENT>(lds + o, p + o);
+  } else {
+    for (int o = 0; o < bytes; o += nth * 16)
+      if (o + lane16 + 16 <= bytes) copy16<COHERENT>(lds + o, p + o);
+  }
+  if (MAX == 0 || MAX % 16 != 0) {
+    const int tail = bytes & ~15;
+    if (tail + 4 * t < bytes) copy4(lds_byte(dst) + tail, static_cast<const char *>(src) + tail + 4 * t);
   }
 }
-constexpr int kCpolAgent = 16;     // sc1: device-coherent access (other XCDs' stores visible)
 
-// 32-bit words of a tile's static block staged through registers during a stage.
-template <typename real>
-__device__ __forceinline__ int stat_head(int nstat) {
-  const int cap = StatRegs<real>::value * int(blockDim.x);
-  return nstat < cap ? nstat : cap;
+// Copies the tile's part of a state array [3][K][M] to [3][E][M] in LDS, one word per lane (its
+// planes have no alignment beyond a value's).
+template <class LT, int M, int EC, typename real>
+__device__ __forceinline__ void copy_state(real *dst, const void *src, size_t splane, int k0, int ne, int E) {
+  constexpr int W = sizeof(real) / 4;
+  const int nth = threads<LT>(), plane = E * M * W, live = ne * M * W, t = phase_tid();
+  const uint32_t lds = lds_byte(dst) + (wave_id() << 8);
+  const uint32_t *s0 = static_cast<const uint32_t *>(src) + size_t(k0) * M * W;
+  auto round = [&](int o) {
+    const int i = o + t, c = (i >= plane) + (i >= 2 * plane), w = i - (c == 0 ? 0 : c == 1 ? plane : 2 * plane);
+    if (c < 3 && w < live) copy4(lds + 4 * o, s0 + (c == 0 ? 0 : c == 1 ? splane * W : 2 * splane * W) + w);
+  };
+  if constexpr (EC != 0 && LT::NT != 0) {
+#pragma unroll
+    for (int o = 0; o < 3 * EC * M * W; o += LT::NT) round(o);
+  } else {
+    for (int o = 0; o < 3 * plane; o += nth) round(o);
+  }
 }
 
-// Phase 0: fetch the tile's global data into LDS (all asynchronous; see above).
-template <typename real, int N, bool WADG, bool MULTI>
-__device__ __forceinline__ void fetch_tile(const StageArgs &a, const InstDesc &d, int k0, int ne, Lds<real, N> &L) {
-  constexpr int Np = dim_Np(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N);
-  constexpr int W = sizeof(real) / 4;     // 32-bit words per value
+// Phase 0: fetch the tile's global data into LDS (all asynchronous; see above).  `index`: the
+// tile's number within its instance.
+template <typename real, int N, bool WADG, bool MULTI, int EC, class LT>
+__device__ __forceinline__ void fetch_tile(const StageArgs &a, const StageRun &r, const InstDesc &d, int index, int k0,
+                                           int ne, LT &L) {
+  constexpr int Np = dim_Np(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N), SW = stat_words(N, WADG), B = int(sizeof(real));
+  const int E = L.E;
   const size_t splane = size_t(d.K) * Np;
-  auto words = [](const void *p) { return static_cast<const uint32_t *>(p); };
-  auto lwords = [](real *p) { return reinterpret_cast<uint32_t *>(p); };
   // the multi-stage build runs RK stages only, on the instance buffers (see stage_tile)
-  const int mode = MULTI ? int(kStage) : a.mode;
+  const int mode = MULTI ? int(kStage) : r.mode;
   const void *ext_ut = MULTI ? nullptr : a.ext_ut, *ext_state = MULTI ? nullptr : a.ext_state;
   const void *ext_nbx = MULTI ? nullptr : a.ext_nbx;
   if (mode != kProject) {
-    // u~ and the metric factors are stored tile-blocked ([4][ne][Nh] per tile), one copy each
+    // u~ and the metric factors are stored tile-blocked ([4][E][Nh] per tile), one copy each
     const size_t base = size_t(k0) * 4 * Nh;
-    const void *ut = ext_ut ? ext_ut : d.ut[a.in_buf];
-    async_copy_words(lwords(L.raw), words(static_cast<const real *>(ut) + base), 4 * ne * Nh * W);
-    async_copy_words(lwords(L.raw + 4 * ne * Nh), words(static_cast<const real *>(d.geo) + base), 4 * ne * Nh * W);
+    const void *ut = ext_ut ? ext_ut : d.ut[r.in_buf];
+    copy_block<LT, 4 * EC * Nh * B>(L.raw, static_cast<const real *>(ut) + base, 4 * E * Nh * B);
+    copy_block<LT, 4 * EC * Nh * B>(L.raw + 4 * E * Nh, static_cast<const real *>(d.geo) + base, 4 * E * Nh * B);
+    // neighbour values, pushed here by the neighbours' projections (in a multi-stage launch
+    // during this kernel, maybe on another XCD)
+    const real *nbx = static_cast<const real *>(ext_nbx ? ext_nbx : d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4;
+    copy_block<LT, EC * Nfq * 4 * B, MULTI>(L.nb, nbx, ne * Nfq * 4 * B);
   }
-  if (mode == kStage) {
-    const real *uh = static_cast<const real *>(d.uh);
-    const real *du = static_cast<const real *>(d.du);
-    for (int c = 0; c < 3; ++c) {
-      async_copy_words(lwords(L.U + c * ne * Np), words(uh + c * splane + size_t(k0) * Np), ne * Np * W);
-      async_copy_words(lwords(L.DU + c * ne * Np), words(du + c * splane + size_t(k0) * Np), ne * Np * W);
-    }
-  } else if (mode == kProject) {
-    const real *src = static_cast<const real *>(ext_state ? ext_state : d.uh);
-    for (int c = 0; c < 3; ++c)
-      async_copy_words(lwords(L.U + c * ne * Np), words(src + c * splane + size_t(k0) * Np), ne * Np * W);
-  }
-  {
-    // static block (mass data, w J, b, push targets): contiguous in HBM and in LDS.  A
-    // stage copies only the part beyond the first kStatRegs words per thread here; that head
-    // goes through registers and lands in LDS after the residual (stage_tile).
-    constexpr int SW = stat_words(N, WADG);
-    const int nstat = ne * SW * W, head = mode == kProject ? 0 : stat_head<real>(nstat);
-    async_copy_words(lwords(L.Minv) + head, words(static_cast<const real *>(d.stat) + size_t(k0) * SW) + head,
-                     nstat - head);
-  }
-  if (mode != kProject) {          // neighbour values, pushed here by the neighbours' projections
-    const void *nbx = ext_nbx ? ext_nbx : d.nbx[a.in_buf];
-    const uint32_t *src = words(static_cast<const real *>(nbx) + size_t(k0) * Nfq * 4);
-    if (MULTI && a.progress)       // multi-stage launch: written during this kernel, maybe on another XCD
-      async_copy_words<kCpolAgent>(lwords(L.nb), src, ne * Nfq * 4 * W);
-    else
-      async_copy_words(lwords(L.nb), src, ne * Nfq * 4 * W);
-  }
-  __builtin_amdgcn_s_waitcnt(0);   // this wave's copies have landed in LDS
+  if (mode != kRhs)
+    copy_state<LT, Np, EC>(L.U, mode == kProject && ext_state ? ext_state : d.uh, splane, k0, ne, E);
+  if (mode == kStage) copy_state<LT, Np, EC>(L.DU, d.du, splane, k0, ne, E);
+  // static block (mass data, w J, rest depth, push targets): contiguous in HBM and in LDS
+  copy_block<LT, EC * SW * B>(L.Minv, static_cast<const real *>(d.stat) + size_t(index) * stat_tile(N, E, WADG),
+                              E * SW * B);
+  wait_copies();
 }
 
 // Interface terms of face node f (Section 2.8) from its node record rm and the neighbour's
 // values nbp (h, u, v, H - Href): W_f [ nJ . f_S(u~, u~+) + 1/2 g h (H+ - Href) nJ ] minus,
-// for the LF flux, the penalty 1/2 lambda sJ (u~+ - u~).  One function for the pair loop's
-// face rows and the separate interface pass, so both produce the same bits.
+// for the LF flux, the penalty 1/2 lambda sJ (u~+ - u~).
 template <typename real>
 __device__ __forceinline__ void interface_terms(const real *rm, const real *nbp, real wf, real nrf, real nsf, real g,
                                                 int flux, real &t0, real &t1, real &t2) {
@@ -572,13 +570,12 @@ __device__ __forceinline__ void interface_terms(const real *rm, const real *nbp,
 //   sum_n ({u} c + gh_m dH_n Qx) = u_m a0 + b1 + gh_m q1   (halves folded into the records)
 // Volume rows run over all Nh columns (the diagonal of the skew operator is zero), face rows
 // over the Nq volume columns (the surface-surface block is zero).  This function is one
-// task: rows m0 .. m0+R-1 (r0 .. r0+R-1 within their row set) of element e, over columns
-// [n_lo, n_hi), with the operator table Stab (already offset to row r0) whose consecutive
+// task: rows m0 .. m0+R-1 of element e, over columns [n_lo, n_hi), with the operator table
+// Stab (already offset to the first of these rows of its row set) whose consecutive
 // columns are ld2 reals apart; the sums go to chunk slot p of the residual block.
 template <typename real, int N, int R, class LD, class LT>
-__device__ __forceinline__ void row_sums(const InstDesc &d, int ne, int e, int r0, int m0, int p, bool face,
-                                         int n_lo, int n_hi, const real *Stab, LD ld2, LT &L, bool iface) {
-  constexpr int Nfq = dim_Nfq(N), Nh = dim_Nh(N);
+__device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, int n_hi, const real *Stab, LD ld2, LT &L) {
+  constexpr int Nh = dim_Nh(N);
   typedef real real4 __attribute__((ext_vector_type(4)));
   const real *rbase = L.rec + __umul24(unsigned(e), unsigned(rec_stride(N)));
   real hu[R], hv[R], u[R], v[R], gh[R], rx[R], sx[R], ry[R], sy[R], a0[R], a1[R], a2[R];
@@ -620,20 +617,11 @@ __device__ __forceinline__ void row_sums(const InstDesc &d, int ne, int e, int r
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int m = m0 + r;
-    if (face && p == 0 && iface) {         // interface terms of face row m (else a later pass)
-      const int f = r0 + r;
-      real t0, t1, t2;
-      interface_terms<real>(rbase + m * kNodeRec, L.nb + __umul24(unsigned(e), unsigned(Nfq * 4)) + f * 4, L.wf[f],
-                            L.nr[f], L.ns[f], real(d.g), d.flux, t0, t1, t2);
-      a0[r] = a0[r] + t0;
-      a1[r] = a1[r] + t1;
-      a2[r] = a2[r] + t2;
-    }
     // partial sums of column chunk p
-    real *Rp = L.R + __umul24(unsigned(p), unsigned(3 * ne * Nh)) + __umul24(unsigned(e), unsigned(Nh)) + m;
+    real *Rp = L.R + __umul24(unsigned(p), unsigned(3 * L.E * Nh)) + __umul24(unsigned(e), unsigned(Nh)) + m;
     Rp[0] = a0[r];
-    Rp[ne * Nh] = a1[r];
-    Rp[2 * ne * Nh] = a2[r];
+    Rp[L.E * Nh] = a1[r];
+    Rp[2 * L.E * Nh] = a2[r];
   }
 }
 
@@ -648,11 +636,11 @@ template <int D, int P> __host__ __device__ constexpr int face_chunks() {
 }
 
 template <typename real, int N, int R, int P, class LT>
-__device__ __forceinline__ void residual_tile(const InstDesc &d, int ne, LT &L, bool iface) {
+__device__ __forceinline__ void residual_tile(int ne, LT &L) {
   constexpr int Nq = dim_Nq(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N);
   constexpr int VB = Nq / R, FB = Nfq / R, PF = face_chunks<N, P>();
   static_assert(Nq % R == 0 && Nfq % R == 0, "R must divide Nq and Nfq");
-  const int tid = phase_tid(), nth = blockDim.x;
+  const int tid = phase_tid(), nth = threads<LT>();
   const int nv = ne * VB * P, ntask = nv + ne * FB * PF;
   // task splits in unsigned arithmetic by constants (see FieldTask)
   auto split = [](int t, unsigned parts, unsigned rows, int &p, int &e, int &b) {
@@ -678,8 +666,8 @@ __device__ __forceinline__ void residual_tile(const InstDesc &d, int ne, LT &L, 
       const int ncol = face ? Nq : Nh, n_lo = __umul24(unsigned(p), unsigned(C)),
                 n_hi = n_lo + C < ncol ? n_lo + C : ncol;
       const int r0 = b * R;
-      row_sums<real, N, R>(d, ne, e, r0, face ? Nq + r0 : r0, p, face, n_lo, n_hi,
-                           (face ? L.FT : L.ST) + 2 * r0, face ? 2 * Nfq : 2 * Nq, L, iface);
+      row_sums<real, N, R>(e, face ? Nq + r0 : r0, p, n_lo, n_hi, (face ? L.FT : L.ST) + 2 * r0,
+                           face ? 2 * Nfq : 2 * Nq, L);
     } else {
       // column chunk slowest: a wave's lanes then share one column range (the node records
       // of its columns are read by several elements at once, the operator table's rows by
@@ -688,102 +676,45 @@ __device__ __forceinline__ void residual_tile(const InstDesc &d, int ne, LT &L, 
       if (t < nv) {
         split_slow(t, ne * VB, VB, p, e, b);
         const int r0 = b * R;
-        row_sums<real, N, R>(d, ne, e, r0, r0, p, false, int(unsigned(p) * Nh / P), int(unsigned(p + 1) * Nh / P),
-                             L.ST + 2 * r0, std::integral_constant<int, 2 * Nq>(), L, iface);
+        row_sums<real, N, R>(e, r0, p, int(unsigned(p) * Nh / P), int(unsigned(p + 1) * Nh / P), L.ST + 2 * r0,
+                             std::integral_constant<int, 2 * Nq>(), L);
       } else {
         split_slow(t - nv, ne * FB, FB, p, e, b);
         const int r0 = b * R;
-        row_sums<real, N, R>(d, ne, e, r0, Nq + r0, p, true, int(unsigned(p) * Nq / P), int(unsigned(p + 1) * Nq / P),
-                             L.FT + 2 * r0, std::integral_constant<int, 2 * Nfq>(), L, iface);
+        row_sums<real, N, R>(e, Nq + r0, p, int(unsigned(p) * Nq / P), int(unsigned(p + 1) * Nq / P), L.FT + 2 * r0,
+                             std::integral_constant<int, 2 * Nfq>(), L);
       }
     }
   }
 }
 
-// The residual phase in the instance's tile shape (one of the shapes of shape_ok).
-template <typename real, int N, class LT>
-__device__ __forceinline__ void residual_shaped(const InstDesc &d, int ne, LT &L, bool iface, int shape) {
-  switch (shape) {
-    case make_shape(1, 1): residual_tile<real, N, 1, 1>(d, ne, L, iface); break;
-    case make_shape(1, 2): residual_tile<real, N, 1, 2>(d, ne, L, iface); break;
-    case make_shape(1, 3): residual_tile<real, N, 1, 3>(d, ne, L, iface); break;
-    case make_shape(1, 4): residual_tile<real, N, 1, 4>(d, ne, L, iface); break;
-    default:
-      if constexpr (shape_ok<real, N>(make_shape(2, 1))) {
-        switch (shape) {
-          case make_shape(2, 1): residual_tile<real, N, 2, 1>(d, ne, L, iface); break;
-          case make_shape(2, 2): residual_tile<real, N, 2, 2>(d, ne, L, iface); break;
-          case make_shape(2, 3): residual_tile<real, N, 2, 3>(d, ne, L, iface); break;
-          case make_shape(2, 4): residual_tile<real, N, 2, 4>(d, ne, L, iface); break;
-          default: break;
-        }
+// Residual r_h of column c = (field, element) at hybrid node k: its column chunks and, on the
+// face rows, the interface terms.
+template <typename real, int D, int P, class LT>
+__device__ __forceinline__ auto residual_in(const LT &L) {
+  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), PF = face_chunks<D, P>(), PX = P > PF ? P : PF;
+  const int E = L.E;
+  const real *R = L.R, *nb = L.nb;
+  return [=](int c) {
+    const int f = (c >= E) + (c >= 2 * E), e = c - f * E;
+    const real *pr = R + __umul24(unsigned(c), unsigned(Nh));
+    const real *pf = nb + __umul24(unsigned(e), unsigned(4 * Nfq)) + f;
+    return [=](int k, int s) {     // s = k / 4, which settles most of the tests at compile time
+      real v = pr[k];
+      const bool some = 4 * s + 3 >= Nq, face = 4 * s >= Nq || k >= Nq;
+#pragma unroll
+      for (int p = 1; p < PX; ++p) {
+        const real x = pr[p * 3 * E * Nh + k];
+        if (P == PF) v += x;
+        else v += face ? (p < PF ? x : real(0)) : (p < P ? x : real(0));
       }
-      break;
-  }
-}
-
-// Wide kinds: adds the chunk partial sums of every residual row into chunk 0's (P chunks
-// for volume rows, face_chunks for face rows), once per (field, element, node), so that
-// the lift reads one partial.
-template <typename real, int N, int P, class LT>
-__device__ __forceinline__ void sum_partials(int ne, LT &L) {
-  constexpr int Nq = dim_Nq(N), Nh = dim_Nh(N), PF = face_chunks<N, P>();
-  for (int i = phase_tid(); i < 3 * ne * Nh; i += blockDim.x) {
-    const int n = int(unsigned(i) % unsigned(Nh));
-    real r = L.R[i];
-    if (n < Nq) {
-#pragma unroll
-      for (int p = 1; p < P; ++p) r += L.R[p * 3 * ne * Nh + i];
-    } else {
-#pragma unroll
-      for (int p = 1; p < PF; ++p) r += L.R[p * 3 * ne * Nh + i];
-    }
-    L.R[i] = r;
-  }
-}
-
-// Lift of the residual on the vector ALUs: T = V_h^T r_h, one task per (field, element,
-// mode).  PS partial sums per row are added here (1 once sum_partials has run).
-template <typename real, int N, int PS, class LT>
-__device__ __forceinline__ void lift_valu(int ne, LT &L) {
-  constexpr int Np = dim_Np(N), Nh = dim_Nh(N);
-  for (int i = phase_tid(); i < 3 * ne * Np; i += blockDim.x) {
-    const FieldTask<Np> k(i, ne * Np);
-    const real *Rc = L.R + __umul24(unsigned(k.c), unsigned(ne * Nh)) + __umul24(unsigned(k.e), unsigned(Nh));
-    const real *Vj = L.Vh + k.j;
-    real ya = 0, yb = 0;
-#pragma unroll 32
-    for (int n = 0; n < Nh; ++n) {
-      real rn = Rc[n];
-#pragma unroll
-      for (int p = 1; p < PS; ++p) rn += Rc[p * 3 * ne * Nh + n];
-      if (n & 1) yb += Vj[n * Np] * rn; else ya += Vj[n * Np] * rn;
-    }
-    L.T[i] = ya + yb;
-  }
-}
-
-// The residual's chunk partials reduced to what the lift reads: summed in place for wide
-// kinds (then a barrier), left for the lift otherwise.
-template <typename real, int N, int P, int CM, class LT>
-__device__ __forceinline__ void lift_partials(int ne, LT &L) {
-  constexpr int Np = dim_Np(N), Nh = dim_Nh(N);
-  if constexpr (wide_kind(N) && P > 1) {
-    sum_partials<real, N, P>(ne, L);
-    __syncthreads();
-  }
-  constexpr int PS = wide_kind(N) ? 1 : P;
-  if constexpr (CM != kValu) {
-    gemm_mfma<CM, real>(Np, Nh, 3 * ne, [&](int i, int k) { return L.Vh[k * Np + i]; },
-                        [&](int k, int c) {
-                          real v = L.R[c * Nh + k];
-                          for (int p = 1; p < PS; ++p) v += L.R[p * 3 * ne * Nh + c * Nh + k];
-                          return v;
-                        },
-                        [&](int i, int c, real v) { L.T[c * Np + i] = v; });
-  } else {
-    lift_valu<real, N, PS>(ne, L);
-  }
+      if (some) {
+        const real x = pf[face ? 4 * (k - Nq) : 0];
+        v += face ? x : real(0);
+      }
+      return v;
+    };
+  };
 }
 
 // Descriptors, tiles and tile ranges are written by the host before a launch and only
@@ -829,38 +760,32 @@ __device__ __forceinline__ void publish(const StageArgs &a, int t, int value) {
   if (threadIdx.x == 0) __hip_atomic_store(a.progress + t, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Phase 3: interface terms of the face rows (Section 2.8), added to the first column
-// part of the residual: W_f [ nJ . f_S(u~, u~+) + 1/2 g h (H+ - Href) nJ ] - LF penalty,
-// one task per (element, face node).  A separate pass so that a resident tile can run
-// the whole pair loop before it waits for its neighbours' values.
+// Phase 3: interface terms of the face rows (Section 2.8): W_f [ nJ . f_S(u~, u~+) + 1/2 g h
+// (H+ - Href) nJ ] - LF penalty, one task per (element, face node), written over the
+// neighbour values they are formed from (the lift adds them).  A pass of its own so that a
+// resident tile can run the whole pair loop before it waits for its neighbours' values.
 template <typename real, int N, class LT>
 __device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L) {
-  constexpr int Nq = dim_Nq(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N);
-  for (int i = phase_tid(); i < ne * Nfq; i += blockDim.x) {
-    const int e = int(unsigned(i) / unsigned(Nfq)), f = i - __umul24(unsigned(e), unsigned(Nfq)), m = Nq + f;
-    const int em = __umul24(unsigned(e), unsigned(Nh)) + m;
+  constexpr int Nq = dim_Nq(N), Nfq = dim_Nfq(N);
+  for (int i = phase_tid(); i < ne * Nfq; i += threads<LT>()) {
+    const int e = int(unsigned(i) / unsigned(Nfq)), f = i - __umul24(unsigned(e), unsigned(Nfq));
     real t0, t1, t2;
-    interface_terms<real>(L.rec + __umul24(unsigned(e), unsigned(rec_stride(N))) + m * kNodeRec, L.nb + 4 * i, L.wf[f], L.nr[f],
-                          L.ns[f], real(d.g), d.flux, t0, t1, t2);
-    real *R0 = L.R + em;                  // column part 0 of the three fields
-    R0[0] = R0[0] + t0;
-    R0[ne * Nh] = R0[ne * Nh] + t1;
-    R0[2 * ne * Nh] = R0[2 * ne * Nh] + t2;
+    interface_terms<real>(L.rec + __umul24(unsigned(e), unsigned(rec_stride(N))) + (Nq + f) * kNodeRec, L.nb + 4 * i,
+                          L.wf[f], L.nr[f], L.ns[f], real(d.g), d.flux, t0, t1, t2);
+    L.nb[4 * i] = t0;
+    L.nb[4 * i + 1] = t1;
+    L.nb[4 * i + 2] = t2;
   }
 }
 
-// SHAPES: the build that takes the residual's tile shape from the instance (every shape of
-// shape_ok); without it, the default shape (RowsPerThread rows, DefaultParts column chunks),
-// whose register allocation the other shapes' code does not affect.
-template <typename real, int N, int CM, bool WADG, bool MULTI, bool SHAPES>
-__device__ __forceinline__ bool stage_tile(const StageArgs &a, const InstDesc &d, int k0, int ne, real *sm, real *tile,
-                                           int res = 0, int t = 0, int target = 0) {
-  constexpr int Np = dim_Np(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N);
-  const int tid = phase_tid(), nth = blockDim.x;
-  constexpr int Nq = dim_Nq(N);
-  const int shape = SHAPES ? d.shape : make_shape(RowsPerThread<real, N>::value, DefaultParts<real, N>::value);
-  const int P = SHAPES ? shape_parts(shape) : DefaultParts<real, N>::value;
-  Lds<real, N> L(sm, tile, ne, mass_words(N, WADG), P);
+template <typename real, int N, int CM, bool WADG, bool MULTI, int EC, int NT>
+__device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r, const InstDesc &d, int index, int k0,
+                                           int ne, real *sm, real *tile, int res = 0, int t = 0, int target = 0) {
+  constexpr int Np = dim_Np(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N), P = DefaultParts<real, N>::value;
+  typedef Lds<real, N, EC, NT> LT;
+  const int tid = phase_tid(), nth = threads<LT>();
+  LT L(sm, tile, d.E, mass_words(N, WADG), P);
+  const int E = L.E;
   const real g = real(d.g);
   const bool mid = res & kResMid;                // resident tile after its first stage
   const bool keep = (res & kResident) && !(res & kResLast);   // state stays in LDS only
@@ -868,28 +793,14 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const InstDesc &d
   // returns before any tile): RK stages on the instance buffers.  Taking that as given here
   // compiles the projection-only and RHS paths and the external buffers out of it, whose
   // addresses would otherwise stay live in scalar registers (and spill) across the stage.
-  const int mode = MULTI ? int(kStage) : a.mode;
+  const int mode = MULTI ? int(kStage) : r.mode;
   // a resident tile after its first stage has everything but the neighbour values in LDS;
   // it fetches those after the pair loop, once its neighbours have pushed them
-  if (!mid) fetch_tile<real, N, WADG, MULTI>(a, d, k0, ne, L);
-  // head of the static block: loaded into registers now, while the node records and the
-  // residual run, and written to LDS before the barrier that ends the residual
-  constexpr int W = sizeof(real) / 4;
-  const int nstat = ne * stat_words(N, WADG) * W, head = stat_head<real>(nstat);
-  constexpr int SR = StatRegs<real>::value;
-  const uint32_t *sg = static_cast<const uint32_t *>(d.stat) + size_t(k0) * stat_words(N, WADG) * W;
-  uint32_t sreg[SR];
-  if (mode != kProject && !mid) {
-#pragma unroll
-    for (int j = 0; j < SR; ++j) {
-      const int v = tid + j * nth;
-      sreg[j] = v < head ? sg[v] : 0u;
-    }
-  }
+  if (!mid) fetch_tile<real, N, WADG, MULTI, EC>(a, r, d, index, k0, ne, L);
   if (!MULTI && mode == kProject) {
     __syncthreads();
-    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(a.ext_ut ? a.ext_ut : d.ut[a.out_buf]),
-                              static_cast<real *>(a.ext_nbx ? a.ext_nbx : d.nbx[a.out_buf]), a.flag,
+    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(a.ext_ut ? a.ext_ut : d.ut[r.out_buf]),
+                              static_cast<real *>(a.ext_nbx ? a.ext_nbx : d.nbx[r.out_buf]), a.flag,
                               MULTI && a.progress != nullptr);
     return true;
   }
@@ -899,101 +810,75 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const InstDesc &d
   // phase 1: node records from the fetched u~ and metric factors (a resident tile's
   // previous projection wrote them directly)
   for (int i = tid; i < ne * Nh && !mid; i += nth) {
-    const real h = L.raw[i], u = L.raw[ne * Nh + i], v = L.raw[2 * ne * Nh + i], dH = L.raw[3 * ne * Nh + i];
+    const real h = L.raw[i], u = L.raw[E * Nh + i], v = L.raw[2 * E * Nh + i], dH = L.raw[3 * E * Nh + i];
     typedef real real4 __attribute__((ext_vector_type(4)));
     const int e = int(unsigned(i) / unsigned(Nh)), n = i - __umul24(unsigned(e), unsigned(Nh));
     real4 *rec = reinterpret_cast<real4 *>(L.rec + __umul24(unsigned(e), unsigned(rec_stride(N))) + n * kNodeRec);
     rec[0] = real4{real(0.5) * h * u, real(0.5) * h * v, real(0.5) * u, real(0.5) * v};
-    rec[1] = real4{L.raw[4 * ne * Nh + i], L.raw[5 * ne * Nh + i], L.raw[6 * ne * Nh + i], L.raw[7 * ne * Nh + i]};
+    rec[1] = real4{L.raw[4 * E * Nh + i], L.raw[5 * E * Nh + i], L.raw[6 * E * Nh + i], L.raw[7 * E * Nh + i]};
     rec[2] = real4{real(0.5) * g * h, dH, h, real(0)};
   }
   if (!mid) __syncthreads();
-  if constexpr (SHAPES) residual_shaped<real, N>(d, ne, L, !mid, shape);
-  else residual_tile<real, N, RowsPerThread<real, N>::value, DefaultParts<real, N>::value>(d, ne, L, !mid);
+  residual_tile<real, N, RowsPerThread<real, N>::value, P>(ne, L);
   if (!mid) {
-    uint32_t *sl = reinterpret_cast<uint32_t *>(L.Minv);
-#pragma unroll
-    for (int j = 0; j < SR; ++j) {
-      const int v = tid + j * nth;
-      if (v < head) sl[v] = sreg[j];
-    }
+    interface_tile<real, N>(d, ne, L);
   } else {
     if (!wait_neighbours(a, t, target)) return false;
     // from here to its publish the tile is on its neighbours' critical path (their next
     // stage waits for its pushes), while the other workgroups on the CU that are still in
     // their pair loop have slack: raise this workgroup's wave priority until the publish
     __builtin_amdgcn_s_setprio(2);
-    async_copy_words<kCpolAgent>(reinterpret_cast<uint32_t *>(L.nb),
-                                 static_cast<const uint32_t *>(d.nbx[a.in_buf]) + size_t(k0) * Nfq * 4 * W,
-                                 ne * Nfq * 4 * W);
-    __builtin_amdgcn_s_waitcnt(0);
+    copy_block<LT, EC * Nfq * 4 * int(sizeof(real)), true>(
+        L.nb, static_cast<const real *>(d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4, ne * Nfq * 4 * int(sizeof(real)));
+    wait_copies();
   }
   if (mid) {
     __syncthreads();
     interface_tile<real, N>(d, ne, L);
   }
   __syncthreads();
-  // lift: y = V_h^T r_h (r_h = the sum of the chunk partials), one task per (field, element,
-  // mode)
-  if constexpr (SHAPES) {
-    switch (P) {
-      case 1: lift_partials<real, N, 1, CM>(ne, L); break;
-      case 2: lift_partials<real, N, 2, CM>(ne, L); break;
-      case 3: lift_partials<real, N, 3, CM>(ne, L); break;
-      default: lift_partials<real, N, 4, CM>(ne, L); break;
-    }
-  } else {
-    lift_partials<real, N, DefaultParts<real, N>::value, CM>(ne, L);
-  }
+  // lift: y = V_h^T r_h
+  contract<CM, Np, Nh, Np, true, real>(L.Vh, 3 * E, threads<LT>() >> 6, residual_in<real, N, P>(L), cols_out<Np>(L.T));
   __syncthreads();
   // rhs = -Minv y; store it, or do the LSRK update
   const size_t splane = size_t(d.K) * Np;
   real *uh = static_cast<real *>(d.uh);
   real *du = static_cast<real *>(d.du);
   real *rhs_out = static_cast<real *>(MULTI ? nullptr : a.ext_rhs);
-  const real ra = real(a.rk_a), rdt = real(d.dt), rb = real(a.rk_b);
-  if constexpr (WADG) {            // first factor into the residual block (dead after the lift)
-    wadg_first<real, N>(ne, L, L.T, L.R);
-    __syncthreads();
-  }
-  // one task per (field, element, mode)
-  for (int i = tid; i < 3 * ne * Np; i += nth) {
-    const FieldTask<Np> k(i, ne * Np);
-    real rr;
-    if constexpr (WADG) {
-      rr = -wadg_second<real, N>(L, L.R + __umul24(unsigned(k.c), unsigned(ne * Nq)) +
-                                        __umul24(unsigned(k.e), unsigned(Nq)), k.j);
-    } else {
-      const real *Mi = L.Minv + __umul24(unsigned(k.r), unsigned(Np));   // row (e, j) of Minv_e
-      const real *Tc = L.T + (i - k.j);                                  // T[c][e][0..Np)
-      real ra0 = 0, ra1 = 0;
-#pragma unroll 32
-      for (int m = 0; m + 1 < Np; m += 2) {
-        ra0 -= Mi[m] * Tc[m];
-        ra1 -= Mi[m + 1] * Tc[m + 1];
-      }
-      if (Np & 1) ra0 -= Mi[Np - 1] * Tc[Np - 1];
-      rr = ra0 + ra1;
-    }
+  const real ra = real(r.rk_a), rdt = real(d.dt), rb = real(r.rk_b);
+  // one output per (field, element, mode); elements beyond a ragged tile's ne are dropped
+  auto update = [&](int i, real y) {
+    const real rr = -y;
+    const FieldTask<Np> k(i, E * Np);
     // global index: field c's plane, the tile's first element, then r (zero-extended)
     const size_t o = size_t(unsigned(k.c)) * splane + size_t(k0) * Np + unsigned(k.r);
+    const bool in = k.r < ne * Np;
     if (mode == kRhs) {
-      rhs_out[o] = rr;
+      if (in) rhs_out[o] = rr;
     } else {
       const real dn = ra * L.DU[i] + rdt * rr;
       const real un = L.U[i] + rb * dn;
-      if (!keep) {
+      if (!keep && in) {
         du[o] = dn;
         uh[o] = un;
       }
       L.DU[i] = dn;
       L.U[i] = un;
     }
+  };
+  if constexpr (WADG) {            // first factor into the residual block (dead after the lift)
+    wadg_first<real, N>(L, L.T, L.R);
+    __syncthreads();
+    wadg_second<real, N>(L, L.R, L.T);
+    __syncthreads();
+    for (int i = tid; i < 3 * E * Np; i += nth) update(i, L.T[i]);
+  } else {
+    minv_rows<real, N>(L, L.T, update);
   }
   if (mode == kStage) {
     __syncthreads();
-    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(d.ut[a.out_buf]),
-                              static_cast<real *>(d.nbx[a.out_buf]), a.flag, MULTI && a.progress != nullptr, res);
+    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(d.ut[r.out_buf]),
+                              static_cast<real *>(d.nbx[r.out_buf]), a.flag, MULTI && a.progress != nullptr, res);
   }
   return true;
 }
@@ -1011,11 +896,9 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const InstDesc &d
 // and ends the workgroup; its neighbours' waits then give up in turn.
 // V1: the build that also holds the variant-1 element kinds (N+2 points per direction and
 // per face); launches whose instances are all of variant 0 use the build without them,
-// whose register allocation those larger kinds do not affect.  SHAPES: see stage_tile
-// (built with vector-ALU contractions and variant-0 kinds only).  KIND: a build for one
-// variant-0 kind alone (vector-ALU contractions, default shapes), used when every instance
-// is of that kind: its registers are allocated for that kind's code only (FP32 N=3: 95
-// VGPRs and 86 scalar spills against 122 and 105 for the build of all kinds).
+// whose register allocation those larger kinds do not affect.  KIND: a build for one
+// variant-0 kind alone, used when every instance is of that kind: its registers are
+// allocated for that kind's code only.  EC: a build of that for one tile size.
 // Residency probe of a multi-stage grid (kProbe): every workgroup counts itself in and waits,
 // with a bounded spin, until the whole grid has; a wait that gives up sets flag bit 2.  Run
 // once at bind with the grid, workgroup size and LDS of the multi-stage launches: if every
@@ -1036,16 +919,22 @@ __device__ __forceinline__ void residency_probe(const StageArgs &a) {
   }
 }
 
-template <typename real, int CM, bool WADG, bool MULTI, bool V1, bool SHAPES, int KIND = 0>
+// Threads of a kernel built for one kind (as the host launches it; 0: not a constant).
+__host__ __device__ constexpr int stage_kernel_threads(int kind) {
+  return kind == 0 ? 0 : wide_kind(kind) ? kBlockWide : kBlock;
+}
+
+template <typename real, int CM, bool WADG, bool MULTI, bool V1, int KIND = 0, int EC = 0>
 __global__ void __launch_bounds__(kBlockWide) __attribute__((amdgpu_waves_per_eu(4)))
 stage_kernel(StageArgs a) {
   if (MULTI && a.mode == kProbe) {
     residency_probe(a);
     return;
   }
+  constexpr int NT = stage_kernel_threads(KIND);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   real *sm = reinterpret_cast<real *>(smem_raw);
-  real *tile = sm + a.ref_words_max;
+  real *tile = sm + (KIND != 0 ? (ref_words(KIND) + 3) & ~3 : a.ref_words_max);
   const int G = int(gridDim.x);
   const int chunk = (int(blockIdx.x) % kXcds) * (G / kXcds) + int(blockIdx.x) / kXcds;
   const int t0 = a.ranges ? read_const(a.ranges, chunk) : int((long long)chunk * a.ntiles / G);
@@ -1059,13 +948,13 @@ stage_kernel(StageArgs a) {
   const int nst = multi ? a.nstages : 1;
   int loaded_N = 0;
   for (int s = 0; s < nst; ++s) {
-    StageArgs as = a;
+    StageRun r{a.mode, a.in_buf, a.out_buf, a.rk_a, a.rk_b};
     if (multi) {
-      as.mode = kStage;
-      as.in_buf = (a.in_buf + s) & 1;
-      as.out_buf = 1 - as.in_buf;
-      as.rk_a = a.rk_a5[s % 5];
-      as.rk_b = a.rk_b5[s % 5];
+      r.mode = kStage;
+      r.in_buf = (a.in_buf + s) & 1;
+      r.out_buf = 1 - r.in_buf;
+      r.rk_a = a.rk_a5[s % 5];
+      r.rk_b = a.rk_b5[s % 5];
     }
     for (int t = t0; t < t1; ++t) {
       const int res = resident ? kResident | (s > 0 ? kResMid : 0) | (s == nst - 1 ? kResLast : 0) : 0;
@@ -1077,18 +966,18 @@ stage_kernel(StageArgs a) {
       }
       const Tile tl = read_const(a.tiles, t);
       const InstDesc &d = read_const(a.desc, tl.inst);
-      if (d.N != loaded_N) {
-        __syncthreads();
-        const real *ref = static_cast<const real *>(d.ref);
-        const int words = ref_words(d.N);
-        for (int i = threadIdx.x; i < words; i += blockDim.x) sm[i] = ref[i];
-        loaded_N = d.N;
+      if (KIND != 0 ? loaded_N == 0 : d.N != loaded_N) {
+        // the reference block, copied with the tile's data (which fetch_tile waits for)
+        if (KIND == 0) __syncthreads();
+        constexpr int words = KIND != 0 ? (ref_words(KIND) + 3) & ~3 : 0;
+        copy_block<Threads<NT>, words * int(sizeof(real))>(sm, d.ref, ((ref_words(d.N) + 3) & ~3) * int(sizeof(real)));
+        loaded_N = KIND != 0 ? KIND : d.N;
       }
       bool ok = true;
 #define ESDG_STAGE_CASE(D) \
-  case D: ok = stage_tile<real, D, CM, WADG, MULTI, SHAPES>(as, d, tl.k0, tl.ne, sm, tile, res, t, a.stage0 + s); break;
+  case D: ok = stage_tile<real, D, CM, WADG, MULTI, EC, NT>(a, r, d, tl.index, tl.k0, tl.ne, sm, tile, res, t, a.stage0 + s); break;
       if constexpr (KIND != 0) {     // every tile is of this kind (the host's choice of kernel)
-        switch (d.N) {
+        switch (KIND) {
           ESDG_STAGE_CASE(KIND)
           default: break;
         }
@@ -1195,13 +1084,13 @@ __global__ void __launch_bounds__(kBlock) rest_depth_kernel(DiagArgs a) {
   if (t >= a.ntiles) return;
   const Tile tl = read_const(a.tiles, t);
   const InstDesc &d = read_const(a.desc, tl.inst);
-  const int D = d.N, Nq = dim_Nq(D), Nh = dim_Nh(D), ne = tl.ne;
+  const int D = d.N, Nq = dim_Nq(D), Nh = dim_Nh(D), ne = tl.ne, E = d.E;
   const bool wadg = a.wadg != 0;
-  real *st = static_cast<real *>(const_cast<void *>(d.stat)) + size_t(tl.k0) * stat_words(D, wadg);
+  real *st = static_cast<real *>(const_cast<void *>(d.stat)) + size_t(tl.index) * stat_tile(D, E, wadg);
   // modal kinds: Href - b at the volume nodes, then at the hybrid nodes, after the mass data
   // and w J; DG-SBP: at the volume nodes, after 1/(w J)
-  real *dq = st + ne * (key_sbp(D) ? Nq : mass_words(D, wadg) + Nq);
-  real *dh = dq + ne * Nq;
+  real *dq = st + E * (key_sbp(D) ? Nq : mass_words(D, wadg) + Nq);
+  real *dh = dq + E * Nq;
   for (int i = threadIdx.x; i < ne * Nq; i += blockDim.x) {
     const int e = i / Nq, q = i - e * Nq;
     dq[i] = real(d.Href - d.bd[size_t(tl.k0 + e) * Nh + q]);
@@ -1226,11 +1115,12 @@ __global__ void __launch_bounds__(kBlock) rest_depth_kernel(DiagArgs a) {
 // LDS carve-up of one DG-SBP tile (see tile_words()).
 template <typename real, int D>
 struct LdsSbp {
-  static constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D);
+  static constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), NT = kBlock;
   real *ref, *ST, *FT, *wf, *nr, *ns, *fvol, *vface;
   real *rec, *R, *nb, *U, *DU, *iwJ, *dep, *geo;
   int32_t *pp;
-  __device__ LdsSbp(real *sm, real *tile, int E) {
+  int E;
+  __device__ LdsSbp(real *sm, real *tile, int e) : E(e) {
     ref = sm;
     ST = ref;
     FT = ST + 2 * Nh * Nq;
@@ -1241,13 +1131,13 @@ struct LdsSbp {
     vface = fvol + Nfq;           // face node of volume node n, or -1
     rec = tile;
     R = rec + E * rec_stride(D);  // two column-part partials [2][3][E][Nh]
-    nb = R + 6 * E * Nh;
-    U = nb + 4 * E * Nfq;
-    DU = U + 3 * E * Nq;
-    iwJ = DU + 3 * E * Nq;        // static block: 1/(w J) | rest depth | metrics [4][E][Nq] | push targets
+    nb = R + ((6 * E * Nh + 3) & ~3);   // 16-byte aligned, as the static block after it
+    iwJ = nb + 4 * E * Nfq;       // static block: 1/(w J) | rest depth | metrics [4][E][Nq] | push targets
     dep = iwJ + E * Nq;
     geo = dep + E * Nq;
     pp = reinterpret_cast<int32_t *>(geo + 4 * E * Nq);
+    U = geo + E * (4 * Nq + Nfq);
+    DU = U + 3 * E * Nq;
   }
 };
 
@@ -1259,15 +1149,15 @@ __device__ __forceinline__ void sbp_push(const InstDesc &d, int ne, LdsSbp<real,
   bool bad = false;
   for (int i = phase_tid(); i < ne * Nfq; i += blockDim.x) {
     const int e = i / Nfq, f = i - e * Nfq, j = e * Nq + int(L.fvol[f]);
-    const double eta = L.U[j], hu = L.U[ne * Nq + j], hv = L.U[2 * ne * Nq + j];
+    const double eta = L.U[j], hu = L.U[L.E * Nq + j], hv = L.U[2 * L.E * Nq + j];
     const double h = eta + double(L.dep[j]);
     const double u = hu / h, v = hv / h;
     double pu = u, pv = v;
     const uint32_t tgt = uint32_t(L.pp[i]);
     if (tgt & kPushWall) {
       const double nr = double(L.nr[f]), ns = double(L.ns[f]);
-      const double nx = double(L.geo[j]) * nr + double(L.geo[ne * Nq + j]) * ns;
-      const double ny = double(L.geo[2 * ne * Nq + j]) * nr + double(L.geo[3 * ne * Nq + j]) * ns;
+      const double nx = double(L.geo[j]) * nr + double(L.geo[L.E * Nq + j]) * ns;
+      const double ny = double(L.geo[2 * L.E * Nq + j]) * nr + double(L.geo[3 * L.E * Nq + j]) * ns;
       const double c = 2.0 * (u * nx + v * ny) / (nx * nx + ny * ny);
       pu = u - c * nx;
       pv = v - c * ny;
@@ -1281,29 +1171,24 @@ __device__ __forceinline__ void sbp_push(const InstDesc &d, int ne, LdsSbp<real,
 }
 
 template <typename real, int D>
-__device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, int k0, int ne, real *sm, real *tile) {
-  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), SW = stat_words(D);
-  constexpr int W = sizeof(real) / 4;
-  LdsSbp<real, D> L(sm, tile, ne);
-  const int tid = phase_tid(), nth = blockDim.x;
+__device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, int index, int k0, int ne, real *sm,
+                                         real *tile) {
+  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), SW = stat_words(D);
+  LdsSbp<real, D> L(sm, tile, d.E);
+  const int E = L.E;
+  const int tid = phase_tid(), nth = kBlock;
   const size_t splane = size_t(d.K) * Nq;
-  auto words = [](const void *p) { return static_cast<const uint32_t *>(p); };
-  auto lwords = [](real *p) { return reinterpret_cast<uint32_t *>(p); };
-  {                                // fetch: state, RK register, static block, neighbour values
-    const real *src = static_cast<const real *>(a.ext_state ? a.ext_state : d.uh);
-    const real *du = static_cast<const real *>(d.du);
-    for (int c = 0; c < 3; ++c) {
-      async_copy_words(lwords(L.U + c * ne * Nq), words(src + c * splane + size_t(k0) * Nq), ne * Nq * W);
-      if (a.mode == kStage)
-        async_copy_words(lwords(L.DU + c * ne * Nq), words(du + c * splane + size_t(k0) * Nq), ne * Nq * W);
-    }
-    async_copy_words(lwords(L.iwJ), words(static_cast<const real *>(d.stat) + size_t(k0) * SW), ne * SW * W);
-    if (a.mode != kProject) {
-      const void *nbx = a.ext_nbx ? a.ext_nbx : d.nbx[a.in_buf];
-      async_copy_words(lwords(L.nb), words(static_cast<const real *>(nbx) + size_t(k0) * Nfq * 4), ne * Nfq * 4 * W);
-    }
-    __builtin_amdgcn_s_waitcnt(0);
+  typedef LdsSbp<real, D> LT;
+  // fetch: state, RK register, static block, neighbour values
+  copy_state<LT, Nq, 0>(L.U, a.ext_state ? a.ext_state : d.uh, splane, k0, ne, E);
+  if (a.mode == kStage) copy_state<LT, Nq, 0>(L.DU, d.du, splane, k0, ne, E);
+  copy_block<LT, 0>(L.iwJ, static_cast<const real *>(d.stat) + size_t(index) * stat_tile(D, E, false),
+                    E * SW * int(sizeof(real)));
+  if (a.mode != kProject) {
+    const real *nbx = static_cast<const real *>(a.ext_nbx ? a.ext_nbx : d.nbx[a.in_buf]) + size_t(k0) * Nfq * 4;
+    copy_block<LT, 0>(L.nb, nbx, ne * Nfq * 4 * int(sizeof(real)));
   }
+  wait_copies();
   __syncthreads();
   real *nbx_out = static_cast<real *>(a.ext_nbx ? a.ext_nbx : d.nbx[a.out_buf]);
   if (a.mode == kProject) {
@@ -1315,14 +1200,14 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
   const real g = real(d.g);
   bool bad = false;
   for (int i = tid; i < ne * Nq; i += nth) {
-    const double eta = L.U[i], hu = L.U[ne * Nq + i], hv = L.U[2 * ne * Nq + i];
+    const double eta = L.U[i], hu = L.U[E * Nq + i], hv = L.U[2 * E * Nq + i];
     const double h = eta + double(L.dep[i]);
     const double u = hu / h, v = hv / h;
     const int e = i / Nq, q = i - e * Nq;
     typedef real real4 __attribute__((ext_vector_type(4)));
     real4 *rec = reinterpret_cast<real4 *>(L.rec + e * rec_stride(D) + q * kNodeRec);
     rec[0] = real4{real(0.5 * hu), real(0.5 * hv), real(0.5 * u), real(0.5 * v)};
-    rec[1] = real4{L.geo[i], L.geo[ne * Nq + i], L.geo[2 * ne * Nq + i], L.geo[3 * ne * Nq + i]};
+    rec[1] = real4{L.geo[i], L.geo[E * Nq + i], L.geo[2 * E * Nq + i], L.geo[3 * E * Nq + i]};
     rec[2] = real4{real(0.5) * g * real(h), real(eta), real(h), real(0)};
     bad |= bad_value(h, hu, hv);
   }
@@ -1336,7 +1221,8 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
     reinterpret_cast<real4 *>(L.rec + e * rec_stride(D) + (Nq + f) * kNodeRec)[quad] = srcr[quad];
   }
   __syncthreads();
-  residual_tile<real, D, 1, 2>(d, ne, L, true);
+  residual_tile<real, D, 1, 2>(ne, L);
+  interface_tile<real, D>(d, ne, L);
   __syncthreads();
   // du/dt = -(W J)^{-1} [I; I_f]^T r_h; store it, or do the LSRK update
   real *uh = static_cast<real *>(d.uh);
@@ -1345,23 +1231,21 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
   const real ra = real(a.rk_a), rdt = real(d.dt), rb = real(a.rk_b);
   for (int i = tid; i < 3 * ne * Nq; i += nth) {
     const int c = (i >= ne * Nq) + (i >= 2 * ne * Nq), j = i - c * ne * Nq, e = j / Nq, n = j - e * Nq;
-    const real *R0 = L.R + c * ne * Nh + e * Nh, *R1 = R0 + 3 * ne * Nh;
-    real r = R0[n] + R1[n];
+    const auto rh = residual_in<real, D, 2>(L)(c * E + e);
+    real r = rh(n, n >> 2);
     const int vf = int(L.vface[n]);
-    if (vf >= 0) {                 // face rows have face_chunks<D, 2>() chunk partials
-      r += R0[Nq + vf];
-      if constexpr (face_chunks<D, 2>() > 1) r += R1[Nq + vf];
-    }
+    if (vf >= 0) r += rh(Nq + vf, (Nq + vf) >> 2);
     const real rr = -r * L.iwJ[j];
     const size_t o = size_t(c) * splane + size_t(k0) * Nq + j;
     if (a.mode == kRhs) {
       rhs_out[o] = rr;
     } else {
-      const real dn = ra * L.DU[i] + rdt * rr;
-      const real un = L.U[i] + rb * dn;
+      const int l = c * E * Nq + j;
+      const real dn = ra * L.DU[l] + rdt * rr;
+      const real un = L.U[l] + rb * dn;
       du[o] = dn;
       uh[o] = un;
-      L.U[i] = un;
+      L.U[l] = un;
     }
   }
   if (a.mode == kStage) {
@@ -1395,7 +1279,7 @@ sbp_stage_kernel(StageArgs a) {
     }
     switch (d.N) {
 #define ESDG_SBP_CASE(N) \
-  case make_key(N, 2): sbp_tile<real, make_key(N, 2)>(a, d, tl.k0, tl.ne, sm, tile); break;
+  case make_key(N, 2): sbp_tile<real, make_key(N, 2)>(a, d, tl.index, tl.k0, tl.ne, sm, tile); break;
       ESDG_SBP_CASE(1) ESDG_SBP_CASE(2) ESDG_SBP_CASE(3) ESDG_SBP_CASE(4)
 #undef ESDG_SBP_CASE
       default: break;
@@ -1412,54 +1296,46 @@ sbp_stage_kernel(StageArgs a) {
 // its combination by contraction mode and launch kind.
 #define ESDG_CAT4(a, b, c, d) a##b##c##d
 #define ESDG_UNIT_FN(R, W) ESDG_CAT4(stage_fn_unit_, R, _, W)
-const void *stage_fn_unit_float_0(int cm, bool multi, bool v1, bool shapes, int kind);
-const void *stage_fn_unit_float_1(int cm, bool multi, bool v1, bool shapes, int kind);
-const void *stage_fn_unit_double_0(int cm, bool multi, bool v1, bool shapes, int kind);
-const void *stage_fn_unit_double_1(int cm, bool multi, bool v1, bool shapes, int kind);
+const void *stage_fn_unit_float_0(int cm, bool multi, bool v1, int kind, int tile);
+const void *stage_fn_unit_float_1(int cm, bool multi, bool v1, int kind, int tile);
+const void *stage_fn_unit_double_0(int cm, bool multi, bool v1, int kind, int tile);
+const void *stage_fn_unit_double_1(int cm, bool multi, bool v1, int kind, int tile);
 
 #if defined(ESDG_UNIT_REAL)
 template <bool V1>
 static const void *unit_fn(int cm, bool multi) {
   using real = ESDG_UNIT_REAL;
   constexpr bool W = ESDG_UNIT_WADG != 0;
-  if constexpr (std::is_same<real, double>::value) {
-    if (cm == kMfmaNative)
-      return multi ? reinterpret_cast<const void *>(&stage_kernel<double, kMfmaNative, W, true, V1, false>)
-                   : reinterpret_cast<const void *>(&stage_kernel<double, kMfmaNative, W, false, V1, false>);
-    return multi ? reinterpret_cast<const void *>(&stage_kernel<double, kValu, W, true, V1, false>)
-                 : reinterpret_cast<const void *>(&stage_kernel<double, kValu, W, false, V1, false>);
-  } else {
+  if constexpr (std::is_same<real, float>::value) {
     if (cm == kMfmaBf16x3)
-      return multi ? reinterpret_cast<const void *>(&stage_kernel<float, kMfmaBf16x3, W, true, V1, false>)
-                   : reinterpret_cast<const void *>(&stage_kernel<float, kMfmaBf16x3, W, false, V1, false>);
-    if (cm == kMfmaNative)
-      return multi ? reinterpret_cast<const void *>(&stage_kernel<float, kMfmaNative, W, true, V1, false>)
-                   : reinterpret_cast<const void *>(&stage_kernel<float, kMfmaNative, W, false, V1, false>);
-    return multi ? reinterpret_cast<const void *>(&stage_kernel<float, kValu, W, true, V1, false>)
-                 : reinterpret_cast<const void *>(&stage_kernel<float, kValu, W, false, V1, false>);
+      return multi ? reinterpret_cast<const void *>(&stage_kernel<float, kMfmaBf16x3, W, true, V1>)
+                   : reinterpret_cast<const void *>(&stage_kernel<float, kMfmaBf16x3, W, false, V1>);
   }
+  return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, V1>)
+               : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, V1>);
 }
-template <bool MULTI>
-static const void *kind_fn(int kind) {
+template <int K>
+static const void *kind_fn(bool multi, int tile) {
   using real = ESDG_UNIT_REAL;
   constexpr bool W = ESDG_UNIT_WADG != 0;
-  switch (kind) {
-    case 1: return reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, MULTI, false, false, 1>);
-    case 2: return reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, MULTI, false, false, 2>);
-    case 3: return reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, MULTI, false, false, 3>);
-    case 4: return reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, MULTI, false, false, 4>);
-    case 5: return reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, MULTI, false, false, 5>);
-    default: return nullptr;
-  }
+  constexpr int EC = fixed_tile<real>(K);
+  if (tile == EC)
+    return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, false, K, EC>)
+                 : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, false, K, EC>);
+  return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, false, K>)
+               : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, false, K>);
 }
-const void *ESDG_UNIT_FN(ESDG_UNIT_REAL, ESDG_UNIT_WADG)(int cm, bool multi, bool v1, bool shapes, int kind) {
-  using real = ESDG_UNIT_REAL;
-  constexpr bool W = ESDG_UNIT_WADG != 0;
-  // one variant-0 kind, vector-ALU contractions and its default shape: that kind's own build
-  if (kind >= 1 && kind <= 5 && cm == kValu && !v1 && !shapes) return multi ? kind_fn<true>(kind) : kind_fn<false>(kind);
-  if (shapes)                      // vector-ALU contractions, variant-0 kinds
-    return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, true, false, true>)
-                 : reinterpret_cast<const void *>(&stage_kernel<real, kValu, W, false, false, true>);
+const void *ESDG_UNIT_FN(ESDG_UNIT_REAL, ESDG_UNIT_WADG)(int cm, bool multi, bool v1, int kind, int tile) {
+  if (cm != kMfmaBf16x3 && !v1) {  // one variant-0 kind: that kind's own build
+    switch (kind) {
+      case 1: return kind_fn<1>(multi, tile);
+      case 2: return kind_fn<2>(multi, tile);
+      case 3: return kind_fn<3>(multi, tile);
+      case 4: return kind_fn<4>(multi, tile);
+      case 5: return kind_fn<5>(multi, tile);
+      default: break;
+    }
+  }
   return v1 ? unit_fn<true>(cm, multi) : unit_fn<false>(cm, multi);
 }
 #endif
@@ -1475,10 +1351,10 @@ const void *ESDG_UNIT_FN(ESDG_UNIT_REAL, ESDG_UNIT_WADG)(int cm, bool multi, boo
 // multi-stage instantiation for single stages as well, measured faster then; with the
 // single-kind builds and the current task layout the per-stage one is faster on one box:
 // N=1..5 by 11, 7.5, 6.5, 2 and 2.3 %, the mixed-degree ensemble by 5 %.)
-static const void *stage_fn(bool fp64, int cm, bool wadg, bool multi, bool v1, bool shapes, int kind) {
+static const void *stage_fn(bool fp64, int cm, bool wadg, bool multi, bool v1, int kind, int tile) {
   if (fp64)
-    return wadg ? stage_fn_unit_double_1(cm, multi, v1, shapes, kind) : stage_fn_unit_double_0(cm, multi, v1, shapes, kind);
-  return wadg ? stage_fn_unit_float_1(cm, multi, v1, shapes, kind) : stage_fn_unit_float_0(cm, multi, v1, shapes, kind);
+    return wadg ? stage_fn_unit_double_1(cm, multi, v1, kind, tile) : stage_fn_unit_double_0(cm, multi, v1, kind, tile);
+  return wadg ? stage_fn_unit_float_1(cm, multi, v1, kind, tile) : stage_fn_unit_float_0(cm, multi, v1, kind, tile);
 }
 
 static const void *sbp_fn(bool fp64) {
@@ -1488,7 +1364,7 @@ static const void *sbp_fn(bool fp64) {
 
 // Workgroups of the stage kernel (the DG-SBP kernel with sbp) that stay resident on the
 // whole device.
-hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, bool shapes, int kind, size_t lds_bytes,
+hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile, size_t lds_bytes,
                             int block, int *out) {
   int dev = 0, ncu = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -1506,7 +1382,7 @@ hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, boo
   e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
   if (e != hipSuccess) return e;
   for (int multi = 0; multi < 2; ++multi) {
-    const void *fn = sbp ? sbp_fn(fp64) : stage_fn(fp64, cm, wadg, multi != 0, v1, shapes, kind);
+    const void *fn = sbp ? sbp_fn(fp64) : stage_fn(fp64, cm, wadg, multi != 0, v1, kind, tile);
     int n = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, lds_bytes);
     if (e != hipSuccess) return e;
@@ -1522,13 +1398,13 @@ hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, boo
   return hipSuccess;
 }
 
-hipError_t set_stage_lds_limit(bool fp64, int cm, bool wadg, bool sbp, bool v1, bool shapes, int kind,
+hipError_t set_stage_lds_limit(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile,
                                size_t lds_bytes) {
   if (sbp) return hipFuncSetAttribute(sbp_fn(fp64), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
-  hipError_t e = hipFuncSetAttribute(stage_fn(fp64, cm, wadg, false, v1, shapes, kind),
+  hipError_t e = hipFuncSetAttribute(stage_fn(fp64, cm, wadg, false, v1, kind, tile),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(stage_fn(fp64, cm, wadg, true, v1, shapes, kind), hipFuncAttributeMaxDynamicSharedMemorySize,
+  return hipFuncSetAttribute(stage_fn(fp64, cm, wadg, true, v1, kind, tile), hipFuncAttributeMaxDynamicSharedMemorySize,
                              int(lds_bytes));
 }
 
@@ -1546,7 +1422,7 @@ hipError_t launch_stage(bool fp64, bool sbp, const StageArgs &a, int max_blocks,
   const int grid = stage_grid(a.ntiles, max_blocks);
   StageArgs arg = a;
   void *params[] = {&arg};
-  return hipLaunchKernel(sbp ? sbp_fn(fp64) : stage_fn(fp64, a.contraction, a.wadg != 0, false, a.v1 != 0, a.shapes != 0, a.kind),
+  return hipLaunchKernel(sbp ? sbp_fn(fp64) : stage_fn(fp64, a.contraction, a.wadg != 0, false, a.v1 != 0, a.kind, a.tile),
                          dim3(grid),
                          dim3(sbp ? kBlock : block), params, lds_bytes, stream);
 }
@@ -1559,7 +1435,7 @@ hipError_t launch_stage_fused(bool fp64, const StageArgs &a, int max_blocks, siz
   const int grid = stage_grid(a.ntiles, max_blocks);
   StageArgs arg = a;
   void *params[] = {&arg};
-  const void *fn = stage_fn(fp64, a.contraction, a.wadg != 0, true, a.v1 != 0, a.shapes != 0, a.kind);
+  const void *fn = stage_fn(fp64, a.contraction, a.wadg != 0, true, a.v1 != 0, a.kind, a.tile);
   if (cooperative) return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(block), params, lds_bytes, stream);
   return hipLaunchKernel(fn, dim3(grid), dim3(block), params, lds_bytes, stream);
 }

@@ -19,13 +19,13 @@
 #include "host_setup.hpp"
 
 namespace esdg {
-hipError_t set_stage_lds_limit(bool fp64, int cm, bool wadg, bool sbp, bool v1, bool shapes, int kind,
+hipError_t set_stage_lds_limit(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile,
                                size_t lds_bytes);
 hipError_t launch_stage(bool fp64, bool sbp, const StageArgs &a, int max_blocks, size_t lds_bytes, int block,
                         hipStream_t stream);
 hipError_t launch_stage_fused(bool fp64, const StageArgs &a, int max_blocks, size_t lds_bytes, int block,
                               bool cooperative, hipStream_t stream);
-hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, bool shapes, int kind, size_t lds_bytes,
+hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile, size_t lds_bytes,
                             int block, int *out);
 int stage_grid(int ntiles, int max_blocks);
 hipError_t launch_diag(bool fp64, const DiagArgs &a, hipStream_t stream);
@@ -52,9 +52,11 @@ thread_local std::string g_init_error;
 // array's name, which on the host is a stand-in and not a device address.
 constexpr size_t kScratchBytes = size_t(64) << 20;
 constexpr size_t kScratchHead = 256;       // flag word (int32), padded to the 256-byte alignment
+// the projected values of a last, ragged tile filled up to 64 elements of the largest kind
+constexpr size_t kScratchRagged = size_t(64) * 4 * dim_Nh(make_key(kMaxN, 1)) * sizeof(double);
 }  // namespace
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchRagged];
 
 namespace {
 
@@ -111,7 +113,7 @@ int default_shape(int D, bool fp64) {
   return make_shape(two ? 2 : 1, one ? 1 : 2);
 }
 
-// A tile shape the stage kernel is compiled for (kernels.hip: shape_ok).
+// A tile shape the option takes.
 bool shape_valid(int D, bool fp64, int shape) {
   const int R = shape_rows(shape), P = shape_parts(shape);
   if (P < 1 || P > 4) return false;
@@ -149,10 +151,10 @@ struct esdg_swe {
   bool balanced = false;           // mixed degrees: cost-balanced tile ranges uploaded
   size_t ws_bytes = 0;
   std::map<int, int> epb;          // elements per workgroup per element kind
-  std::map<int, int> shape;        // tile shape of the residual phase per element kind
   size_t lds_bytes = 0;
   int block = kBlock;              // stage-kernel workgroup size (kBlockWide if every kind is wide)
   int kind = 0;                    // the one element kind of every instance (modal), else 0
+  int tile = 0;                    // its elements per tile
   bool cooperative = true;         // multi-stage launches through hipLaunchCooperativeKernel (false
                                    // once the residency probe at bind saw the whole grid resident)
   int ref_max = 0;                 // LDS words reserved for the largest reference block
@@ -256,8 +258,8 @@ StageArgs base_args(esdg_swe *s, int inst) {
   a.contraction = s->contraction;
   a.wadg = s->wadg ? 1 : 0;
   a.v1 = s->v1 ? 1 : 0;
-  a.shapes = s->shapes ? 1 : 0;
   a.kind = s->kind;
+  a.tile = s->tile;
   return a;
 }
 
@@ -505,17 +507,17 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
                      " not compiled (rows 1, or 2 in float where they divide Nq and Nfq; parts 1..4)";
       return ESDG_EINVAL;
     }
-    s->shape[D] = shape;
     if (!s->sbp && shape != default_shape(D, s->fp64)) s->shapes = true;
     const int P = shape_parts(shape);
     int E = opt->elems_per_block[N] ? opt->elems_per_block[N] : default_epb(D, s->word, s->wadg, P, s->block);
     s->epb[D] = E;
+    if (D == s->kind) s->tile = E;
     s->ref_max = std::max(s->ref_max, ref_words(D));
     tile = std::max(tile, size_t(tile_words(D, E, s->wadg, P)));
   }
   if (s->shapes && (s->contraction != 0 || s->v1)) {
-    g_init_error = "esdg_swe_init: tile shapes other than the default are compiled with vector-ALU contractions "
-                   "and (N+1)-point quadrature only";
+    g_init_error = "esdg_swe_init: tile shapes other than the default need matrix_cores 0 or 1, FP64 or FP32 "
+                   "and the (N+1)-point quadrature";
     return ESDG_EINVAL;
   }
   s->ref_max = (s->ref_max + 3) & ~3;
@@ -531,7 +533,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
   for (int i = 0; i < n_inst; ++i) {
     const int E = s->epb[s->host[i].key];
     s->tile_begin[i] = int(s->tiles.size());
-    for (int k0 = 0; k0 < inst[i].K; k0 += E) s->tiles.push_back(Tile{i, k0, std::min(E, inst[i].K - k0), 0});
+    for (int k0 = 0; k0 < inst[i].K; k0 += E) s->tiles.push_back(Tile{i, k0, std::min(E, inst[i].K - k0), k0 / E});
     s->tile_count[i] = int(s->tiles.size()) - s->tile_begin[i];
   }
   // tiles holding face neighbours of each tile (for fused multi-stage launches)
@@ -571,12 +573,13 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     Offsets &f = s->off[i];
     f.uh = take(3 * K * Np * w);
     f.du = take(3 * K * Np * w);
-    for (int b = 0; b < 3; ++b) f.ut[b] = s->sbp ? 0 : take(4 * K * Nh * w);
+    const size_t KE = size_t(s->tile_count[i]) * s->epb[D];   // elements, the last tile filled up
+    for (int b = 0; b < 3; ++b) f.ut[b] = s->sbp ? 0 : take(4 * KE * Nh * w);
     for (int b = 0; b < 3; ++b) f.nbx[b] = take(4 * K * Nfq * w);
-    f.geo = s->sbp ? 0 : take(4 * K * Nh * w);
+    f.geo = s->sbp ? 0 : take(4 * KE * Nh * w);
     f.wJq = take(K * Nq * sizeof(double));
     f.bd = take(K * Nh * sizeof(double));
-    f.stat = take(K * size_t(stat_words(D, s->wadg)) * w);
+    f.stat = take(size_t(s->tile_count[i]) * stat_tile(D, s->epb[D], s->wadg) * w);
     f.rhs = take(3 * K * Np * w);
   }
   s->tiles_off = take(s->tiles.size() * sizeof(Tile));
@@ -606,11 +609,11 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     if (e != hipSuccess) return s->hip_fail(e, "hipGetSymbolAddress (scratch)");
   }
   if (s->lds_bytes > 64 * 1024) {
-    hipError_t e = set_stage_lds_limit(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->shapes, s->kind, s->lds_bytes);
+    hipError_t e = set_stage_lds_limit(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, s->lds_bytes);
     if (e != hipSuccess) return s->hip_fail(e, "hipFuncSetAttribute (LDS)");
   }
   {
-    hipError_t e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->shapes, s->kind, s->lds_bytes, s->block,
+    hipError_t e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, s->lds_bytes, s->block,
                                     &s->max_blocks);
     if (e != hipSuccess) return s->hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (std::getenv("ESDG_SWE_VERBOSE")) {
@@ -640,13 +643,14 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     const InstanceHost &H = s->host[i];
     const Offsets &f = s->off[i];
     if (!s->sbp) {
-      // metric factors in tile-blocked order: [4][ne][Nh] per tile, from k0 * 4 * Nh
+      // metric factors in tile-blocked order: [4][E][Nh] per tile, from k0 * 4 * Nh
       const size_t Nh = size_t(dim_Nh(H.key)), plane = size_t(H.K) * Nh;
-      std::vector<double> g(H.geo.size());
+      const size_t E = size_t(s->epb[H.key]);
+      std::vector<double> g(size_t(s->tile_count[i]) * E * 4 * Nh, 0.0);
       for (int t = s->tile_begin[i]; t < s->tile_begin[i] + s->tile_count[i]; ++t) {
         const size_t k0 = size_t(s->tiles[t].k0), ne = size_t(s->tiles[t].ne);
         for (size_t c = 0; c < 4; ++c)
-          for (size_t j = 0; j < ne * Nh; ++j) g[k0 * 4 * Nh + c * ne * Nh + j] = H.geo[c * plane + k0 * Nh + j];
+          for (size_t j = 0; j < ne * Nh; ++j) g[k0 * 4 * Nh + c * E * Nh + j] = H.geo[c * plane + k0 * Nh + j];
       }
       keep.push_back(to_bulk(g, s->fp64));
       if ((st = upload(s, f.geo, keep.back().data(), keep.back().size()))) return st;
@@ -672,47 +676,44 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
       }
       // static blocks in tile order (the layout of the tile's LDS region from the mass data on);
       // the rest depth Href - b is written by the device at every set_state (here: -b)
-      const size_t SW = size_t(stat_words(D, s->wadg)), word = s->word;
-      std::vector<unsigned char> blk(size_t(H.K) * SW * word, 0);
+      const size_t word = s->word, E = size_t(s->epb[D]), ST = size_t(stat_tile(D, int(E), s->wadg));
+      std::vector<unsigned char> blk(size_t(s->tile_count[i]) * ST * word, 0);
       auto put = [&](size_t real_index, double v) {
         if (s->fp64) std::memcpy(&blk[real_index * 8], &v, 8);
         else { const float f32 = float(v); std::memcpy(&blk[real_index * 4], &f32, 4); }
       };
       for (int t = s->tile_begin[i]; t < s->tile_begin[i] + s->tile_count[i]; ++t) {
-        const int k0 = s->tiles[t].k0, ne = s->tiles[t].ne;
-        size_t o = size_t(k0) * SW;
-        if (s->sbp) {              // 1/(w J) | -b | rxJ, sxJ, ryJ, syJ [4][ne][Nq] at the volume nodes
+        const size_t k0 = size_t(s->tiles[t].k0), ne = size_t(s->tiles[t].ne);
+        size_t o = size_t(s->tiles[t].index) * ST;
+        // an array [E][m] of the block from x [K][m]
+        auto put_rows = [&](const double *x, size_t m, auto value) {
+          for (size_t j = 0; j < ne * m; ++j) put(o + j, value(x[k0 * m + j]));
+          o += E * m;
+        };
+        auto same = [](double v) { return v; };
+        auto minus = [](double v) { return -v; };
+        if (s->sbp) {              // 1/(w J) | -b | rxJ, sxJ, ryJ, syJ [4][E][Nq] at the volume nodes
           const size_t plane = size_t(H.K) * Nh;
-          for (int e = 0; e < ne; ++e)
-            for (int q = 0; q < Nq; ++q) put(o++, 1.0 / H.wJq[size_t(k0 + e) * Nq + q]);
-          for (int e = 0; e < ne; ++e)
-            for (int q = 0; q < Nq; ++q) put(o++, -H.bq[size_t(k0 + e) * Nq + q]);
-          for (int c = 0; c < 4; ++c)
-            for (int e = 0; e < ne; ++e)
-              for (int q = 0; q < Nq; ++q) put(o++, H.geo[c * plane + size_t(k0 + e) * Nh + q]);
+          put_rows(H.wJq.data(), Nq, [](double v) { return 1.0 / v; });
+          put_rows(H.bq.data(), Nq, minus);
+          for (int c = 0; c < 4; ++c, o += E * Nq)
+            for (size_t e = 0; e < ne; ++e)
+              for (int q = 0; q < Nq; ++q) put(o + e * Nq + q, H.geo[c * plane + (k0 + e) * Nh + q]);
         } else {
-          if (s->wadg) {           // w/J at the volume nodes
-            for (int e = 0; e < ne; ++e)
-              for (int q = 0; q < Nq; ++q) put(o++, H.wOverJ[size_t(k0 + e) * Nq + q]);
-          } else {                 // the stored inverse curved mass matrices
-            for (int e = 0; e < ne; ++e)
-              for (int j = 0; j < Np * Np; ++j) put(o++, H.Minv[size_t(k0 + e) * Np * Np + j]);
-          }
-          for (int e = 0; e < ne; ++e)
-            for (int q = 0; q < Nq; ++q) put(o++, H.wJq[size_t(k0 + e) * Nq + q]);
-          for (int e = 0; e < ne; ++e)
-            for (int q = 0; q < Nq; ++q) put(o++, -H.bq[size_t(k0 + e) * Nq + q]);
-          for (int e = 0; e < ne; ++e)
-            for (int n = 0; n < Nh; ++n) put(o++, -H.bh[size_t(k0 + e) * Nh + n]);
+          if (s->wadg) put_rows(H.wOverJ.data(), Nq, same);    // w/J at the volume nodes
+          else put_rows(H.Minv.data(), size_t(Np) * Np, same); // the stored inverse curved mass matrices
+          put_rows(H.wJq.data(), Nq, same);
+          put_rows(H.bq.data(), Nq, minus);
+          put_rows(H.bh.data(), Nh, minus);
         }
-        std::memcpy(&blk[o * word], &push[size_t(k0) * Nfq], size_t(ne) * Nfq * 4);
+        std::memcpy(&blk[o * word], &push[k0 * Nfq], ne * Nfq * 4);
       }
       keep.push_back(std::move(blk));
       if ((st = upload(s, f.stat, keep.back().data(), keep.back().size()))) return st;
     }
     InstDesc &d = s->desc[i];
     d.N = H.key;
-    d.shape = s->shape[H.key];
+    d.E = s->epb[H.key];
     d.K = H.K;
     d.flux = s->opt.flux;
     d.g = s->opt.g;
@@ -904,7 +905,8 @@ esdg_status esdg_swe_rhs_noalloc(esdg_swe *s, int32_t inst, const void *state_de
   StageArgs a = base_args(s, inst);
   a.flag = reinterpret_cast<int32_t *>(base);
   a.ext_ut = base + kScratchHead;
-  a.ext_nbx = base + kScratchHead + ((size_t(4) * H.K * dim_Nh(H.key) * s->word + 255) & ~size_t(255));
+  a.ext_nbx = base + kScratchHead +
+              align256(size_t(4) * s->tile_count[inst] * s->epb[H.key] * dim_Nh(H.key) * s->word);
   a.mode = kProject;
   a.ext_state = state_dev;
   s->scratch_used = true;
