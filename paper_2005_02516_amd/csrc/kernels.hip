@@ -219,10 +219,10 @@ struct Lds {
   int32_t *pp;
   int E;                           // elements of a full tile: the stride of every array below
   // sm: the ref block (already loaded); tile: the tile region (after the largest ref block);
-  // mw: reals of mass data per element (mass_words); P: column parts of the residual.
+  // mw: reals of mass data per element (mass_words).
   // EC: E where the kernel is built for one tile size, so that every offset is an immediate;
   // 0: E is e.
-  __device__ Lds(real *sm, real *tile, int e, int mw, int P) : E(EC != 0 ? EC : e) {
+  __device__ Lds(real *sm, real *tile, int e, int mw) : E(EC != 0 ? EC : e) {
     ref = sm;
     Vh = ref;
     ST = Vh + Nh * Np;
@@ -232,7 +232,7 @@ struct Lds {
     ns = nr + Nfq;
     rec = tile;
     raw = rec + E * rec_stride(N);
-    nb = raw + E * raw_words(N, P);
+    nb = raw + E * raw_words(N, 2);
     Minv = nb + 4 * E * Nfq;     // the static block; every region up to here is 16-byte aligned
     wJ = Minv + E * mw;          // Minv: [E][Np][Np], or w/J [E][Nq] (weight-adjusted)
     bq = wJ + E * Nq;
@@ -243,8 +243,8 @@ struct Lds {
     // reuse: the residual, lift and projection temporaries live in the raw block (dead
     // after phase 1) and v'_h in the neighbour block (dead after the residual); the
     // node records and the state are left alone, so a resident tile keeps them
-    R = raw;                      // the P partial residuals [P][3][E][Nh]
-    T = raw + 3 * P * E * Nh;     // [3][E][Np]
+    R = raw;                      // the two parts of the residual [2][3][E][Nh]
+    T = raw + 6 * E * Nh;         // [3][E][Np]
     Q = raw;                      // [3][E][Nq] projection's weighted entropy variables
     VH = nb;                      // [3][E][Np] v'_h (3 Np <= 4 Nfq for N <= 5)
   }
@@ -255,12 +255,8 @@ struct Lds {
 template <typename real, int N> struct RowsPerThread { static constexpr int value = 1; };
 template <> struct RowsPerThread<float, 1> { static constexpr int value = 2; };
 template <> struct RowsPerThread<float, 3> { static constexpr int value = 2; };
-// Column chunks of the residual phase: one at N = 5 (whose 512-thread workgroups
-// have a task per row already), else two.
-template <typename real, int N> struct DefaultParts { static constexpr int value = 2; };
-template <> struct DefaultParts<float, 5> { static constexpr int value = 1; };
-template <> struct DefaultParts<double, 5> { static constexpr int value = 1; };
-
+template <> struct RowsPerThread<float, make_key(1, 2)> { static constexpr int value = 2; };   // DG-SBP: 6 + 6 nodes
+template <> struct RowsPerThread<float, make_key(3, 2)> { static constexpr int value = 2; };   // 18 + 12
 // The tile size the single-kind kernel of a kind is built for (0: none).
 template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) {
   return sizeof(real) == 4 ? (kind == 1 ? 32 : kind == 2 ? 14 : kind == 3 ? 8 : kind == 4 ? 5 : kind == 5 ? 7 : 0)
@@ -570,12 +566,13 @@ __device__ __forceinline__ void interface_terms(const real *rm, const real *nbp,
 //   sum_n ({u} c + gh_m dH_n Qx) = u_m a0 + b1 + gh_m q1   (halves folded into the records)
 // Volume rows run over all Nh columns (the diagonal of the skew operator is zero), face rows
 // over the Nq volume columns (the surface-surface block is zero).  This function is one
-// task: rows m0 .. m0+R-1 of element e, over columns [n_lo, n_hi), with the operator table
-// Stab (already offset to the first of these rows of its row set) whose consecutive
-// columns are ld2 reals apart; the sums go to chunk slot p of the residual block.
-template <typename real, int N, int R, class LD, class LT>
-__device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, int n_hi, const real *Stab, LD ld2, LT &L) {
-  constexpr int Nh = dim_Nh(N);
+// task: rows m0 .. m0+R-1 of element e, over T columns from n_lo on (one more with `more`),
+// with the operator table Stab (already offset to the first of these rows of its row set)
+// whose consecutive columns are LD2 reals apart; the sums go to part p of the residual block.
+// The trip count is a constant so that the loads of several columns are in flight at once.
+template <typename real, int N, int R, int T, int LD2, class LT>
+__device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, bool more, const real *Stab, LT &L) {
+  constexpr int Nh = dim_Nh(N), UN = T <= 16 ? T : T % 9 == 0 ? 9 : T % 10 == 0 ? 10 : 8;
   typedef real real4 __attribute__((ext_vector_type(4)));
   const real *rbase = L.rec + __umul24(unsigned(e), unsigned(rec_stride(N)));
   real hu[R], hv[R], u[R], v[R], gh[R], rx[R], sx[R], ry[R], sy[R], a0[R], a1[R], a2[R];
@@ -589,13 +586,12 @@ __device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, int n_h
     gh[r] = rm[8];
     a0[r] = 0; b1[r] = 0; b2[r] = 0; q1[r] = 0; q2[r] = 0;
   }
-#pragma unroll 2
-  for (int n = n_lo; n < n_hi; ++n) {
-    const real *rn = rbase + n * kNodeRec;
+  const real *rcol = rbase + __umul24(unsigned(n_lo), unsigned(kNodeRec));
+  const real *Scol = Stab + __umul24(unsigned(n_lo), unsigned(LD2));
+  auto column = [&](const real *rn, const real *S) {
     const real4 c0 = *reinterpret_cast<const real4 *>(rn), c1 = *reinterpret_cast<const real4 *>(rn + 4);
     const real hun = c0.x, hvn = c0.y, un = c0.z, vn = c0.w, dHn = rn[9];
     const real rxn = c1.x, sxn = c1.y, ryn = c1.z, syn = c1.w;
-    const real *S = Stab + n * ld2;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const real Sr = S[2 * r], Ss = S[2 * r + 1];
@@ -608,7 +604,10 @@ __device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, int n_h
       q1[r] += dHn * Qx;
       q2[r] += dHn * Qy;
     }
-  }
+  };
+#pragma unroll UN
+  for (int j = 0; j < T; ++j) column(rcol + j * kNodeRec, Scol + j * LD2);
+  if (more) column(rcol + T * kNodeRec, Scol + T * LD2);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     a1[r] = u[r] * a0[r] + b1[r] + gh[r] * q1[r];
@@ -617,7 +616,6 @@ __device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, int n_h
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int m = m0 + r;
-    // partial sums of column chunk p
     real *Rp = L.R + __umul24(unsigned(p), unsigned(3 * L.E * Nh)) + __umul24(unsigned(e), unsigned(Nh)) + m;
     Rp[0] = a0[r];
     Rp[L.E * Nh] = a1[r];
@@ -625,90 +623,77 @@ __device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, int n_h
   }
 }
 
-// Two task layouts for the residual rows.  Kinds with few hybrid nodes cut volume and face
-// rows each into P chunks, and their tasks fill separate waves (volume tasks first), each
-// row type with its own compile-time loop.  Kinds with many (wide_kind) cut both row
-// types into chunks of one length (residual_chunk), so that volume and face tasks sharing
-// a wave run about the same trip count through one loop; the chunk partials are then
-// summed once (sum_partials) instead of in every lift task.
-template <int D, int P> __host__ __device__ constexpr int face_chunks() {
-  return wide_kind(D) ? residual_face_parts(D, P) : P;
-}
-
-template <typename real, int N, int R, int P, class LT>
+// The tasks of the residual rows; every row's columns are summed in two parts.
+//
+// Kinds with few hybrid nodes cut volume rows (Nh columns) and face rows (Nq columns) into
+// halves, R rows to a task, volume tasks first and the half slowest: a wave then runs one
+// column range (the node records of its columns are read by several elements at once, the
+// operator table's rows by consecutive row blocks).
+//
+// The wide kinds (N=5, and N+2 points at N=4 and 5) have more rows than threads at that cut.
+// There the first tasks (padded to whole waves) take the Nq volume columns of a volume row,
+// and the second ones its Nfq face columns and then half a face row (Nq >= 2 Nfq), so that
+// all run about Nq columns: at N=5 and seven elements per workgroup 504 of 512 threads run
+// 36 columns each, against 378 threads running 54 or 36.
+template <typename real, int N, int R, class LT>
 __device__ __forceinline__ void residual_tile(int ne, LT &L) {
   constexpr int Nq = dim_Nq(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N);
-  constexpr int VB = Nq / R, FB = Nfq / R, PF = face_chunks<N, P>();
+  constexpr int VB = Nq / R, FB = Nfq / R;
   static_assert(Nq % R == 0 && Nfq % R == 0, "R must divide Nq and Nfq");
   const int tid = phase_tid(), nth = threads<LT>();
-  const int nv = ne * VB * P, ntask = nv + ne * FB * PF;
-  // task splits in unsigned arithmetic by constants (see FieldTask)
-  auto split = [](int t, unsigned parts, unsigned rows, int &p, int &e, int &b) {
-    const unsigned rest = unsigned(t) / parts;
-    p = t - __umul24(rest, parts);
-    e = int(rest / rows);
-    b = int(rest) - __umul24(unsigned(e), rows);
-  };
-  // chunk slowest: task t = (p ne + e) rows + b with per = ne rows tasks per chunk, P <= 4
-  auto split_slow = [](int t, int per, unsigned rows, int &p, int &e, int &b) {
-    p = (t >= per) + (t >= 2 * per) + (t >= 3 * per);
-    const unsigned rest = unsigned(t - __umul24(unsigned(p), unsigned(per)));
-    e = int(rest / rows);
-    b = int(rest) - __umul24(unsigned(e), rows);
-  };
-  for (int t = tid; t < ntask; t += nth) {
-    if constexpr (wide_kind(N)) {
-      constexpr int C = residual_chunk(N, P);
-      const bool face = t >= nv;
-      int p, e, b;
-      if (face) split(t - nv, PF, FB, p, e, b);
-      else split(t, P, VB, p, e, b);
-      const int ncol = face ? Nq : Nh, n_lo = __umul24(unsigned(p), unsigned(C)),
-                n_hi = n_lo + C < ncol ? n_lo + C : ncol;
-      const int r0 = b * R;
-      row_sums<real, N, R>(e, face ? Nq + r0 : r0, p, n_lo, n_hi, (face ? L.FT : L.ST) + 2 * r0,
-                           face ? 2 * Nfq : 2 * Nq, L);
-    } else {
-      // column chunk slowest: a wave's lanes then share one column range (the node records
-      // of its columns are read by several elements at once, the operator table's rows by
-      // consecutive row blocks), where chunk-fastest lanes read columns Nh / P apart
+  if constexpr (wide_kind(N)) {
+    static_assert(R == 1 && Nq >= 2 * Nfq, "a second task takes one half of a face row");
+    const int rows = ne * Nq, second = (rows + 63) & ~63;
+    for (int t = tid; t < second + rows; t += nth) {
+      const bool b = t >= second;
+      const int i = b ? t - second : t, e = int(unsigned(i) / unsigned(Nq)), m = i - __umul24(unsigned(e), unsigned(Nq));
+      if (!b) {
+        if (i < rows) row_sums<real, N, 1, Nq, 2 * Nq>(e, m, 0, 0, false, L.ST + 2 * m, L);
+      } else {
+        row_sums<real, N, 1, Nfq, 2 * Nq>(e, m, 1, Nq, false, L.ST + 2 * m, L);
+        const int f = m >> 1, h = m & 1;
+        if (m < 2 * Nfq)
+          row_sums<real, N, 1, Nq / 2, 2 * Nfq>(e, Nq + f, h, h * (Nq / 2), Nq % 2 != 0 && h != 0, L.FT + 2 * f, L);
+      }
+    }
+  } else {
+    // task t = (half ne + e) rows + b, split in unsigned arithmetic by constants (see FieldTask)
+    auto split = [&](int t, unsigned rows, int &p, int &e, int &b) {
+      const int per = ne * rows;
+      p = t >= per;
+      const unsigned rest = unsigned(p ? t - per : t);
+      e = int(rest / rows);
+      b = int(rest) - __umul24(unsigned(e), rows);
+    };
+    const int nv = 2 * ne * VB, ntask = nv + 2 * ne * FB;
+    for (int t = tid; t < ntask; t += nth) {
       int p, e, b;
       if (t < nv) {
-        split_slow(t, ne * VB, VB, p, e, b);
-        const int r0 = b * R;
-        row_sums<real, N, R>(e, r0, p, int(unsigned(p) * Nh / P), int(unsigned(p + 1) * Nh / P), L.ST + 2 * r0,
-                             std::integral_constant<int, 2 * Nq>(), L);
+        split(t, VB, p, e, b);
+        row_sums<real, N, R, Nh / 2, 2 * Nq>(e, b * R, p, p * (Nh / 2), Nh % 2 != 0 && p != 0, L.ST + 2 * b * R, L);
       } else {
-        split_slow(t - nv, ne * FB, FB, p, e, b);
-        const int r0 = b * R;
-        row_sums<real, N, R>(e, Nq + r0, p, int(unsigned(p) * Nq / P), int(unsigned(p + 1) * Nq / P), L.FT + 2 * r0,
-                             std::integral_constant<int, 2 * Nfq>(), L);
+        split(t - nv, FB, p, e, b);
+        row_sums<real, N, R, Nq / 2, 2 * Nfq>(e, Nq + b * R, p, p * (Nq / 2), Nq % 2 != 0 && p != 0, L.FT + 2 * b * R, L);
       }
     }
   }
 }
 
-// Residual r_h of column c = (field, element) at hybrid node k: its column chunks and, on the
-// face rows, the interface terms.
-template <typename real, int D, int P, class LT>
+// Residual r_h of column c = (field, element) at hybrid node k: its two parts and, on the face
+// rows, the interface terms.
+template <typename real, int D, class LT>
 __device__ __forceinline__ auto residual_in(const LT &L) {
-  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), PF = face_chunks<D, P>(), PX = P > PF ? P : PF;
+  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D);
   const int E = L.E;
   const real *R = L.R, *nb = L.nb;
   return [=](int c) {
     const int f = (c >= E) + (c >= 2 * E), e = c - f * E;
-    const real *pr = R + __umul24(unsigned(c), unsigned(Nh));
+    const real *p0 = R + __umul24(unsigned(c), unsigned(Nh)), *p1 = p0 + 3 * E * Nh;
     const real *pf = nb + __umul24(unsigned(e), unsigned(4 * Nfq)) + f;
     return [=](int k, int s) {     // s = k / 4, which settles most of the tests at compile time
-      real v = pr[k];
-      const bool some = 4 * s + 3 >= Nq, face = 4 * s >= Nq || k >= Nq;
-#pragma unroll
-      for (int p = 1; p < PX; ++p) {
-        const real x = pr[p * 3 * E * Nh + k];
-        if (P == PF) v += x;
-        else v += face ? (p < PF ? x : real(0)) : (p < P ? x : real(0));
-      }
-      if (some) {
+      real v = p0[k] + p1[k];
+      if (4 * s + 3 >= Nq) {
+        const bool face = 4 * s >= Nq || k >= Nq;
         const real x = pf[face ? 4 * (k - Nq) : 0];
         v += face ? x : real(0);
       }
@@ -781,10 +766,10 @@ __device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L)
 template <typename real, int N, int CM, bool WADG, bool MULTI, int EC, int NT>
 __device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r, const InstDesc &d, int index, int k0,
                                            int ne, real *sm, real *tile, int res = 0, int t = 0, int target = 0) {
-  constexpr int Np = dim_Np(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N), P = DefaultParts<real, N>::value;
+  constexpr int Np = dim_Np(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N);
   typedef Lds<real, N, EC, NT> LT;
   const int tid = phase_tid(), nth = threads<LT>();
-  LT L(sm, tile, d.E, mass_words(N, WADG), P);
+  LT L(sm, tile, d.E, mass_words(N, WADG));
   const int E = L.E;
   const real g = real(d.g);
   const bool mid = res & kResMid;                // resident tile after its first stage
@@ -819,7 +804,7 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r
     rec[2] = real4{real(0.5) * g * h, dH, h, real(0)};
   }
   if (!mid) __syncthreads();
-  residual_tile<real, N, RowsPerThread<real, N>::value, P>(ne, L);
+  residual_tile<real, N, RowsPerThread<real, N>::value>(ne, L);
   if (!mid) {
     interface_tile<real, N>(d, ne, L);
   } else {
@@ -838,7 +823,7 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r
   }
   __syncthreads();
   // lift: y = V_h^T r_h
-  contract<CM, Np, Nh, Np, true, real>(L.Vh, 3 * E, threads<LT>() >> 6, residual_in<real, N, P>(L), cols_out<Np>(L.T));
+  contract<CM, Np, Nh, Np, true, real>(L.Vh, 3 * E, threads<LT>() >> 6, residual_in<real, N>(L), cols_out<Np>(L.T));
   __syncthreads();
   // rhs = -Minv y; store it, or do the LSRK update
   const size_t splane = size_t(d.K) * Np;
@@ -1221,7 +1206,7 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
     reinterpret_cast<real4 *>(L.rec + e * rec_stride(D) + (Nq + f) * kNodeRec)[quad] = srcr[quad];
   }
   __syncthreads();
-  residual_tile<real, D, 1, 2>(ne, L);
+  residual_tile<real, D, RowsPerThread<real, D>::value>(ne, L);
   interface_tile<real, D>(d, ne, L);
   __syncthreads();
   // du/dt = -(W J)^{-1} [I; I_f]^T r_h; store it, or do the LSRK update
@@ -1231,7 +1216,7 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
   const real ra = real(a.rk_a), rdt = real(d.dt), rb = real(a.rk_b);
   for (int i = tid; i < 3 * ne * Nq; i += nth) {
     const int c = (i >= ne * Nq) + (i >= 2 * ne * Nq), j = i - c * ne * Nq, e = j / Nq, n = j - e * Nq;
-    const auto rh = residual_in<real, D, 2>(L)(c * E + e);
+    const auto rh = residual_in<real, D>(L)(c * E + e);
     real r = rh(n, n >> 2);
     const int vf = int(L.vface[n]);
     if (vf >= 0) r += rh(Nq + vf, (Nq + vf) >> 2);
