@@ -10,8 +10,10 @@ constexpr int kMaxN = 5;
 constexpr int kBlock = 256;        // threads per workgroup (4 wave64s)
 constexpr int kBlockWide = 512;    // stage-kernel workgroups of launches whose kinds are all
                                    // wide (wide_kind): 8 wave64s sharing one reference block
-constexpr int kNodeRec = 12;       // per hybrid node in LDS: hu/2 hv/2 u/2 v/2 | rxJ sxJ ryJ syJ | gh/2 dH h -
-                                   // (three aligned quads, so a column is read with two 16-byte loads)
+// Node records in LDS, per hybrid node i = e Nh + n of the tile: the quads q0 = hu/2 hv/2 u/2 v/2
+// and q1 = rxJ sxJ ryJ syJ (kNodeQuads arrays [E][Nh][4], so a column is read with two 16-byte
+// loads and q1 is copied straight from HBM), and the scalars dH and p = gh/2 ([E][Nh] each).
+constexpr int kNodeQuads = 2;
 constexpr int kProbeWord = 16;     // int32 word of the flag block counting a residency probe
 constexpr int kXcds = 8;           // MI355X accelerator complex dies (each with its own L2)
 
@@ -98,7 +100,7 @@ __host__ __device__ constexpr int stat_words(int D, bool wadg = false) {
 }
 
 // Tile shape option of the ABI: rows per thread R and column parts P, packed as (R << 4) | P.
-// It is checked, and P enters the LDS of a tile; the residual runs in its default shape.
+// It is checked, and P enters the tile size limit; the residual has one shape.
 __host__ __device__ constexpr int shape_rows(int shape) { return shape >> 4; }
 __host__ __device__ constexpr int shape_parts(int shape) { return shape & 15; }
 __host__ __device__ constexpr int make_shape(int R, int P) { return (R << 4) | P; }
@@ -108,32 +110,27 @@ __host__ __device__ constexpr int make_shape(int R, int P) { return (R << 4) | P
 // elements sharing one copy of it), and their residual rows use balanced column chunks.
 __host__ __device__ constexpr bool wide_kind(int D) { return !key_sbp(D) && dim_Nh(D) >= 50; }
 
-// Reals per element of the block that holds the fetched u~ and metric factors [8][Nh]
-// (dead after the node records) and then the P residual partials [P][3][Nh] and the lift's
-// output [3][Np].
-__host__ __device__ constexpr int raw_words(int D, int P) {
-  return 8 * dim_Nh(D) > 3 * P * dim_Nh(D) + 3 * dim_Np(D) ? 8 * dim_Nh(D) : 3 * P * dim_Nh(D) + 3 * dim_Np(D);
-}
-
-// Reals of one element's node records in LDS: Nh records of kNodeRec, padded so that the
-// stride is an odd multiple of 4 words.  The residual's lanes read the records of up to
-// eight elements at one column at once; with such a stride their 16-byte reads fall on
-// eight different groups of four banks (an even multiple, e.g. 336 at N=3, puts elements
-// two apart on the same banks).
-__host__ __device__ constexpr int rec_stride(int D) {
-  return dim_Nh(D) * kNodeRec + (dim_Nh(D) % 2 == 0 ? 4 : 0);
-}
+// Reals per element of the block that holds the fetched u~ [4][Nh] (dead after the node
+// records) and then the two parts of the residual [2][3][Nh] and the lift's output [3][Np].
+__host__ __device__ constexpr int raw_words(int D) { return 6 * dim_Nh(D) + 3 * dim_Np(D); }
 
 // Words (of the bulk precision) of LDS one tile of E elements of kind D needs (the
-// reference block is held separately, once per workgroup).  Modal kinds: node records
-// [E][rec_stride] | raw block [E][raw_words] | neighbour values [E][Nfq][4] | static
-// block [E][stat_words] | state, RK register [3][E][Np] each.  DG-SBP: node records | two
-// residual partials [2][3][E][Nh] | neighbour values | state, RK register [3][E][Nq] each |
-// static block.
-__host__ __device__ constexpr int tile_words(int D, int E, bool wadg = false, int P = 2) {
-  return key_sbp(D) ? E * (rec_stride(D) + 4 * dim_Nfq(D) + 6 * dim_Nq(D) + stat_words(D)) + ((6 * E * dim_Nh(D) + 3) & ~3)
-                    : E * (rec_stride(D) + raw_words(D, P) + 4 * dim_Nfq(D) + 6 * dim_Np(D) +
-                           stat_words(D, wadg));
+// reference block is held separately, once per workgroup).  Modal kinds: node quads
+// [2][E][Nh][4] | raw block [E][raw_words] | neighbour values [E][Nfq][4] | static block
+// [E][stat_words] | state, RK register [3][E][Np] each | node scalars [2][E][Nh].  DG-SBP: node
+// quads | two parts of the residual [2][3][E][Nh] | neighbour values | static block | state, RK
+// register [3][E][Nq] each | node scalars.
+__host__ __device__ constexpr int tile_words(int D, int E, bool wadg = false) {
+  return E * ((4 * kNodeQuads + 2) * dim_Nh(D) + 4 * dim_Nfq(D) + 6 * dim_Np(D) + stat_words(D, wadg)) +
+         ((E * (key_sbp(D) ? 6 * dim_Nh(D) : raw_words(D)) + 3) & ~3);
+}
+
+// The tile size limit of the ABI: E elements with P column parts are accepted if this many
+// words and the reference block fit 160 KiB.  tile_words is below it for every kind.
+__host__ __device__ constexpr int limit_words(int D, int E, bool wadg, int P) {
+  const int rec = 12 * dim_Nh(D) + (dim_Nh(D) % 2 == 0 ? 4 : 0), parts = 3 * P * dim_Nh(D) + 3 * dim_Np(D);
+  const int raw = key_sbp(D) ? 6 * dim_Nh(D) : parts > 8 * dim_Nh(D) ? parts : 8 * dim_Nh(D);
+  return E * (rec + raw + 4 * dim_Nfq(D) + 6 * dim_Np(D) + stat_words(D, wadg));
 }
 
 // Reals from one tile's static block to the next in HBM: its words, filled up to 16 bytes.
@@ -152,7 +149,7 @@ struct InstDesc {
                        // (two stage buffers + rhs scratch)
   void *nbx[3];        // [K][Nfq][4] the same four values at each face node's neighbour, written
                        // by the neighbour's projection (one per ut buffer)
-  const void *geo;     // rxJ, sxJ, ryJ, syJ at the hybrid nodes, tile-blocked like ut
+  const void *geo;     // rxJ, sxJ, ryJ, syJ at the hybrid nodes [K][Nh][4] (to the end of the last tile)
   const void *wJq;     // [K][Nq] w_q J in double (diagnostics)
   const void *stat;    // static data in tile order: tile `index` of the instance holds, from
                        // real index * stat_tile(N, E, wadg): the mass data [E][mass_words] (Minv

@@ -214,7 +214,7 @@ struct Lds {
   static constexpr int NT = NTH;
   static constexpr int Np = dim_Np(N), Nq = dim_Nq(N), Nfq = dim_Nfq(N), Nh = dim_Nh(N);
   real *ref, *Vh, *ST, *FT, *wf, *nr, *ns;
-  real *rec, *raw, *nb, *U, *DU, *Minv, *wJ, *bq, *bh;
+  real *q0, *q1, *dH, *p, *raw, *nb, *U, *DU, *Minv, *wJ, *bq, *bh;
   real *R, *T, *Q, *VH;
   int32_t *pp;
   int E;                           // elements of a full tile: the stride of every array below
@@ -230,9 +230,10 @@ struct Lds {
     wf = FT + 2 * Nq * Nfq;
     nr = wf + Nfq;
     ns = nr + Nfq;
-    rec = tile;
-    raw = rec + E * rec_stride(N);
-    nb = raw + E * raw_words(N, 2);
+    q0 = tile;                   // node records (see kNodeQuads)
+    q1 = q0 + 4 * E * Nh;
+    raw = q1 + 4 * E * Nh;
+    nb = raw + ((E * raw_words(N) + 3) & ~3);
     Minv = nb + 4 * E * Nfq;     // the static block; every region up to here is 16-byte aligned
     wJ = Minv + E * mw;          // Minv: [E][Np][Np], or w/J [E][Nq] (weight-adjusted)
     bq = wJ + E * Nq;
@@ -240,6 +241,8 @@ struct Lds {
     pp = reinterpret_cast<int32_t *>(bh + E * Nh);
     U = bh + E * (Nh + Nfq);
     DU = U + 3 * E * Np;
+    dH = DU + 3 * E * Np;
+    p = dH + E * Nh;
     // reuse: the residual, lift and projection temporaries live in the raw block (dead
     // after phase 1) and v'_h in the neighbour block (dead after the residual); the
     // node records and the state are left alone, so a resident tile keeps them
@@ -297,6 +300,15 @@ template <typename real, int N, class LT>
 __device__ __forceinline__ void wadg_second(const LT &L, const real *S, real *out) {
   constexpr int Np = dim_Np(N), Nq = dim_Nq(N);
   contract<kMfmaNative, Np, Nq, Np, true, real>(L.Vh, 3 * L.E, threads<LT>() >> 6, cols_in<Nq, real>(S), cols_out<Np>(out));
+}
+
+// Node record i = e Nh + n (its metric quad q1 is copied there as it lies in HBM).
+template <typename real, class LT>
+__device__ __forceinline__ void write_record(const LT &L, int i, real h, real u, real v, real dH, real g) {
+  typedef real real4 __attribute__((ext_vector_type(4)));
+  reinterpret_cast<real4 *>(L.q0)[i] = real4{real(0.5) * h * u, real(0.5) * h * v, real(0.5) * u, real(0.5) * v};
+  L.dH[i] = dH;
+  L.p[i] = real(0.5) * g * h;
 }
 
 // The stored inverses applied to X [3][E][Np]: store(i, (Minv_e X[c][e])[j]), i = (c E + e) Np + j,
@@ -374,11 +386,7 @@ __device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, 
     const double dH = (v1 + 0.5 * (v2 * v2 + v3 * v3)) / g;
     const double h = dH + double(L.bh[i]);        // L.bh: rest depth Href - b
     if (to_records) {
-      typedef real real4 __attribute__((ext_vector_type(4)));
-      const real hr = real(h), ur = real(v2), vr = real(v3), gr = real(d.g);
-      real4 *rec = reinterpret_cast<real4 *>(L.rec + __umul24(unsigned(e), unsigned(rec_stride(N))) + n * kNodeRec);
-      rec[0] = real4{real(0.5) * hr * ur, real(0.5) * hr * vr, real(0.5) * ur, real(0.5) * vr};
-      rec[2] = real4{real(0.5) * gr * hr, real(dH), hr, real(0)};
+      write_record<real>(L, i, real(h), real(v2), real(v3), real(dH), real(d.g));
     } else {
       real *ot = out + size_t(k0) * 4 * Nh + unsigned(i);   // tile-blocked [4][E][Nh]
       ot[0] = real(h);
@@ -396,10 +404,10 @@ __device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, 
         // normal velocity reversed, u+ = u - 2 (u . nJ) nJ / |nJ|^2, h+ = h (so H+ = H),
         // written into this node's own slot; nJ from the metric factors (tile-blocked, as
         // fetched) and the reference normal of the face
-        const real *gm = static_cast<const real *>(d.geo) + size_t(k0) * 4 * Nh + unsigned(i);
+        const real *gm = static_cast<const real *>(d.geo) + (size_t(k0) * Nh + unsigned(i)) * 4;
         const double nr = double(L.nr[f]), ns = double(L.ns[f]);
-        const double nx = double(gm[0]) * nr + double(gm[E * Nh]) * ns;
-        const double ny = double(gm[2 * E * Nh]) * nr + double(gm[3 * E * Nh]) * ns;
+        const double nx = double(gm[0]) * nr + double(gm[1]) * ns;
+        const double ny = double(gm[2]) * nr + double(gm[3]) * ns;
         const double c = 2.0 * (v2 * nx + v3 * ny) / (nx * nx + ny * ny);
         pu = v2 - c * nx;
         pv = v3 - c * ny;
@@ -508,11 +516,11 @@ __device__ __forceinline__ void fetch_tile(const StageArgs &a, const StageRun &r
   const void *ext_ut = MULTI ? nullptr : a.ext_ut, *ext_state = MULTI ? nullptr : a.ext_state;
   const void *ext_nbx = MULTI ? nullptr : a.ext_nbx;
   if (mode != kProject) {
-    // u~ and the metric factors are stored tile-blocked ([4][E][Nh] per tile), one copy each
+    // u~ and the metric quads are stored tile-blocked ([4][E][Nh] and [E][Nh][4] per tile)
     const size_t base = size_t(k0) * 4 * Nh;
     const void *ut = ext_ut ? ext_ut : d.ut[r.in_buf];
     copy_block<LT, 4 * EC * Nh * B>(L.raw, static_cast<const real *>(ut) + base, 4 * E * Nh * B);
-    copy_block<LT, 4 * EC * Nh * B>(L.raw + 4 * E * Nh, static_cast<const real *>(d.geo) + base, 4 * E * Nh * B);
+    copy_block<LT, 4 * EC * Nh * B>(L.q1, static_cast<const real *>(d.geo) + base, 4 * E * Nh * B);
     // neighbour values, pushed here by the neighbours' projections (in a multi-stage launch
     // during this kernel, maybe on another XCD)
     const real *nbx = static_cast<const real *>(ext_nbx ? ext_nbx : d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4;
@@ -527,15 +535,15 @@ __device__ __forceinline__ void fetch_tile(const StageArgs &a, const StageRun &r
   wait_copies();
 }
 
-// Interface terms of face node f (Section 2.8) from its node record rm and the neighbour's
+// Interface terms of a face node (Section 2.8) from its node record i and the neighbour's
 // values nbp (h, u, v, H - Href): W_f [ nJ . f_S(u~, u~+) + 1/2 g h (H+ - Href) nJ ] minus,
 // for the LF flux, the penalty 1/2 lambda sJ (u~+ - u~).
-template <typename real>
-__device__ __forceinline__ void interface_terms(const real *rm, const real *nbp, real wf, real nrf, real nsf, real g,
+template <typename real, class LT>
+__device__ __forceinline__ void interface_terms(const LT &L, int i, const real *nbp, real wf, real nrf, real nsf, real g,
                                                 int flux, real &t0, real &t1, real &t2) {
   typedef real real4 __attribute__((ext_vector_type(4)));
-  const real4 s0 = *reinterpret_cast<const real4 *>(rm), s1 = *reinterpret_cast<const real4 *>(rm + 4);
-  const real gh = rm[8], dH = rm[9], h = rm[10];
+  const real4 s0 = reinterpret_cast<const real4 *>(L.q0)[i], s1 = reinterpret_cast<const real4 *>(L.q1)[i];
+  const real gh = L.p[i], dH = L.dH[i];          // gh/2, H - Href
   const real nJx = s1.x * nrf + s1.y * nsf, nJy = s1.z * nrf + s1.w * nsf;
   const real uu = real(2) * s0.z, vv = real(2) * s0.w, huu = real(2) * s0.x, hvv = real(2) * s0.y;
   const real hP = nbp[0], uP = nbp[1], vP = nbp[2], dHP = nbp[3];
@@ -548,7 +556,7 @@ __device__ __forceinline__ void interface_terms(const real *rm, const real *nbp,
   real f2v = nJx * hua * va + nJy * (hva * va + pr);
   if (flux == 1) {
     const real sJ = sqrt(nJx * nJx + nJy * nJy);
-    const real lm = fabs(uu * nJx + vv * nJy) + sqrt(g * h) * sJ;
+    const real lm = fabs(uu * nJx + vv * nJy) + sqrt(real(2) * gh) * sJ;
     const real lp = fabs(uP * nJx + vP * nJy) + sqrt(g * hP) * sJ;
     const real c = real(0.5) * fmax(lm, lp);
     f0v -= c * (dHP - dH);
@@ -562,8 +570,8 @@ __device__ __forceinline__ void interface_terms(const real *rm, const real *nbp,
 
 // Residual rows (Section 2.8, flux differencing plus interface terms).  Row m accumulates,
 // over its columns n, c = Qx {hu} + Qy {hv} (a0), u_n c and v_n c (b1, b2), and dH_n Qx,
-// dH_n Qy (q1, q2); the row factors are applied once at the end:
-//   sum_n ({u} c + gh_m dH_n Qx) = u_m a0 + b1 + gh_m q1   (halves folded into the records)
+// dH_n Qy (d1, d2); the row factors are applied once at the end:
+//   sum_n ({u} c + gh_m dH_n Qx) = u_m a0 + b1 + gh_m d1   (halves folded into the records)
 // Volume rows run over all Nh columns (the diagonal of the skew operator is zero), face rows
 // over the Nq volume columns (the surface-surface block is zero).  This function is one
 // task: rows m0 .. m0+R-1 of element e, over T columns from n_lo on (one more with `more`),
@@ -574,23 +582,26 @@ template <typename real, int N, int R, int T, int LD2, class LT>
 __device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, bool more, const real *Stab, LT &L) {
   constexpr int Nh = dim_Nh(N), UN = T <= 16 ? T : T % 9 == 0 ? 9 : T % 10 == 0 ? 10 : 8;
   typedef real real4 __attribute__((ext_vector_type(4)));
-  const real *rbase = L.rec + __umul24(unsigned(e), unsigned(rec_stride(N)));
+  const int i0 = __umul24(unsigned(e), unsigned(Nh));    // the element's first node
+  const real4 *q0 = reinterpret_cast<const real4 *>(L.q0) + i0, *q1 = reinterpret_cast<const real4 *>(L.q1) + i0;
+  const real *dH = L.dH + i0;
   real hu[R], hv[R], u[R], v[R], gh[R], rx[R], sx[R], ry[R], sy[R], a0[R], a1[R], a2[R];
-  real b1[R], b2[R], q1[R], q2[R];
+  real b1[R], b2[R], d1[R], d2[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const real *rm = rbase + (m0 + r) * kNodeRec;
-    const real4 s0 = *reinterpret_cast<const real4 *>(rm), s1 = *reinterpret_cast<const real4 *>(rm + 4);
+    const real4 s0 = q0[m0 + r], s1 = q1[m0 + r];
     hu[r] = s0.x; hv[r] = s0.y; u[r] = s0.z; v[r] = s0.w;
     rx[r] = s1.x; sx[r] = s1.y; ry[r] = s1.z; sy[r] = s1.w;
-    gh[r] = rm[8];
-    a0[r] = 0; b1[r] = 0; b2[r] = 0; q1[r] = 0; q2[r] = 0;
+    gh[r] = L.p[i0 + m0 + r];
+    a0[r] = 0; b1[r] = 0; b2[r] = 0; d1[r] = 0; d2[r] = 0;
   }
-  const real *rcol = rbase + __umul24(unsigned(n_lo), unsigned(kNodeRec));
   const real *Scol = Stab + __umul24(unsigned(n_lo), unsigned(LD2));
-  auto column = [&](const real *rn, const real *S) {
-    const real4 c0 = *reinterpret_cast<const real4 *>(rn), c1 = *reinterpret_cast<const real4 *>(rn + 4);
-    const real hun = c0.x, hvn = c0.y, un = c0.z, vn = c0.w, dHn = rn[9];
+  const real4 *p0 = q0 + n_lo, *p1 = q1 + n_lo;
+  const real *pd = dH + n_lo;
+  auto column = [&](int j) {
+    const real4 c0 = p0[j], c1 = p1[j];
+    const real hun = c0.x, hvn = c0.y, un = c0.z, vn = c0.w, dHn = pd[j];
+    const real *S = Scol + j * LD2;
     const real rxn = c1.x, sxn = c1.y, ryn = c1.z, syn = c1.w;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
@@ -601,22 +612,22 @@ __device__ __forceinline__ void row_sums(int e, int m0, int p, int n_lo, bool mo
       a0[r] += c;
       b1[r] += un * c;
       b2[r] += vn * c;
-      q1[r] += dHn * Qx;
-      q2[r] += dHn * Qy;
+      d1[r] += dHn * Qx;
+      d2[r] += dHn * Qy;
     }
   };
 #pragma unroll UN
-  for (int j = 0; j < T; ++j) column(rcol + j * kNodeRec, Scol + j * LD2);
-  if (more) column(rcol + T * kNodeRec, Scol + T * LD2);
+  for (int j = 0; j < T; ++j) column(j);
+  if (more) column(T);
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    a1[r] = u[r] * a0[r] + b1[r] + gh[r] * q1[r];
-    a2[r] = v[r] * a0[r] + b2[r] + gh[r] * q2[r];
+    a1[r] = u[r] * a0[r] + b1[r] + gh[r] * d1[r];
+    a2[r] = v[r] * a0[r] + b2[r] + gh[r] * d2[r];
   }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int m = m0 + r;
-    real *Rp = L.R + __umul24(unsigned(p), unsigned(3 * L.E * Nh)) + __umul24(unsigned(e), unsigned(Nh)) + m;
+    real *Rp = L.R + __umul24(unsigned(p), unsigned(3 * L.E * Nh)) + i0 + m;
     Rp[0] = a0[r];
     Rp[L.E * Nh] = a1[r];
     Rp[2 * L.E * Nh] = a2[r];
@@ -755,8 +766,8 @@ __device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L)
   for (int i = phase_tid(); i < ne * Nfq; i += threads<LT>()) {
     const int e = int(unsigned(i) / unsigned(Nfq)), f = i - __umul24(unsigned(e), unsigned(Nfq));
     real t0, t1, t2;
-    interface_terms<real>(L.rec + __umul24(unsigned(e), unsigned(rec_stride(N))) + (Nq + f) * kNodeRec, L.nb + 4 * i,
-                          L.wf[f], L.nr[f], L.ns[f], real(d.g), d.flux, t0, t1, t2);
+    interface_terms<real>(L, __umul24(unsigned(e), unsigned(dim_Nh(N))) + Nq + f, L.nb + 4 * i, L.wf[f], L.nr[f], L.ns[f],
+                          real(d.g), d.flux, t0, t1, t2);
     L.nb[4 * i] = t0;
     L.nb[4 * i + 1] = t1;
     L.nb[4 * i + 2] = t2;
@@ -792,17 +803,10 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r
   // a resident tile after its first stage skips the fetch and the records: what its residual
   // reads (the node records) was written before the barrier of the previous stage's publish
   if (!mid) __syncthreads();
-  // phase 1: node records from the fetched u~ and metric factors (a resident tile's
-  // previous projection wrote them directly)
-  for (int i = tid; i < ne * Nh && !mid; i += nth) {
-    const real h = L.raw[i], u = L.raw[E * Nh + i], v = L.raw[2 * E * Nh + i], dH = L.raw[3 * E * Nh + i];
-    typedef real real4 __attribute__((ext_vector_type(4)));
-    const int e = int(unsigned(i) / unsigned(Nh)), n = i - __umul24(unsigned(e), unsigned(Nh));
-    real4 *rec = reinterpret_cast<real4 *>(L.rec + __umul24(unsigned(e), unsigned(rec_stride(N))) + n * kNodeRec);
-    rec[0] = real4{real(0.5) * h * u, real(0.5) * h * v, real(0.5) * u, real(0.5) * v};
-    rec[1] = real4{L.raw[4 * E * Nh + i], L.raw[5 * E * Nh + i], L.raw[6 * E * Nh + i], L.raw[7 * E * Nh + i]};
-    rec[2] = real4{real(0.5) * g * h, dH, h, real(0)};
-  }
+  // phase 1: node records from the fetched u~ (a resident tile's previous projection wrote
+  // them directly)
+  for (int i = tid; i < ne * Nh && !mid; i += nth)
+    write_record<real>(L, i, L.raw[i], L.raw[E * Nh + i], L.raw[2 * E * Nh + i], L.raw[3 * E * Nh + i], g);
   if (!mid) __syncthreads();
   residual_tile<real, N, RowsPerThread<real, N>::value>(ne, L);
   if (!mid) {
@@ -1102,7 +1106,7 @@ template <typename real, int D>
 struct LdsSbp {
   static constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), NT = kBlock;
   real *ref, *ST, *FT, *wf, *nr, *ns, *fvol, *vface;
-  real *rec, *R, *nb, *U, *DU, *iwJ, *dep, *geo;
+  real *q0, *q1, *dH, *p, *R, *nb, *U, *DU, *iwJ, *dep, *geo;
   int32_t *pp;
   int E;
   __device__ LdsSbp(real *sm, real *tile, int e) : E(e) {
@@ -1114,8 +1118,9 @@ struct LdsSbp {
     ns = nr + Nfq;
     fvol = ns + Nfq;              // volume node of face node f (integer-valued reals)
     vface = fvol + Nfq;           // face node of volume node n, or -1
-    rec = tile;
-    R = rec + E * rec_stride(D);  // two column-part partials [2][3][E][Nh]
+    q0 = tile;
+    q1 = q0 + 4 * E * Nh;
+    R = q1 + 4 * E * Nh;          // two parts of the residual [2][3][E][Nh]
     nb = R + ((6 * E * Nh + 3) & ~3);   // 16-byte aligned, as the static block after it
     iwJ = nb + 4 * E * Nfq;       // static block: 1/(w J) | rest depth | metrics [4][E][Nq] | push targets
     dep = iwJ + E * Nq;
@@ -1123,6 +1128,8 @@ struct LdsSbp {
     pp = reinterpret_cast<int32_t *>(geo + 4 * E * Nq);
     U = geo + E * (4 * Nq + Nfq);
     DU = U + 3 * E * Nq;
+    dH = DU + 3 * E * Nq;
+    p = dH + E * Nh;
   }
 };
 
@@ -1158,7 +1165,7 @@ __device__ __forceinline__ void sbp_push(const InstDesc &d, int ne, LdsSbp<real,
 template <typename real, int D>
 __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, int index, int k0, int ne, real *sm,
                                          real *tile) {
-  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), SW = stat_words(D);
+  constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), SW = stat_words(D);
   LdsSbp<real, D> L(sm, tile, d.E);
   const int E = L.E;
   const int tid = phase_tid(), nth = kBlock;
@@ -1190,20 +1197,23 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
     const double u = hu / h, v = hv / h;
     const int e = i / Nq, q = i - e * Nq;
     typedef real real4 __attribute__((ext_vector_type(4)));
-    real4 *rec = reinterpret_cast<real4 *>(L.rec + e * rec_stride(D) + q * kNodeRec);
-    rec[0] = real4{real(0.5 * hu), real(0.5 * hv), real(0.5 * u), real(0.5 * v)};
-    rec[1] = real4{L.geo[i], L.geo[E * Nq + i], L.geo[2 * E * Nq + i], L.geo[3 * E * Nq + i]};
-    rec[2] = real4{real(0.5) * g * real(h), real(eta), real(h), real(0)};
+    const int r = e * Nh + q;
+    reinterpret_cast<real4 *>(L.q0)[r] = real4{real(0.5 * hu), real(0.5 * hv), real(0.5 * u), real(0.5 * v)};
+    reinterpret_cast<real4 *>(L.q1)[r] = real4{L.geo[i], L.geo[E * Nq + i], L.geo[2 * E * Nq + i], L.geo[3 * E * Nq + i]};
+    L.dH[r] = real(eta);
+    L.p[r] = real(0.5) * g * real(h);
     bad |= bad_value(h, hu, hv);
   }
   if (bad) atomicOr(a.flag, 1);
   __syncthreads();
   // the face nodes' records are those of the volume nodes they coincide with
-  for (int i = tid; i < ne * Nfq * 3; i += nth) {
-    const int quad = i % 3, ef = i / 3, e = ef / Nfq, f = ef - e * Nfq;
+  for (int i = tid; i < ne * Nfq; i += nth) {
+    const int e = i / Nfq, f = i - e * Nfq, to = e * Nh + Nq + f, from = e * Nh + int(L.fvol[f]);
     typedef real real4 __attribute__((ext_vector_type(4)));
-    const real4 *srcr = reinterpret_cast<const real4 *>(L.rec + e * rec_stride(D) + int(L.fvol[f]) * kNodeRec);
-    reinterpret_cast<real4 *>(L.rec + e * rec_stride(D) + (Nq + f) * kNodeRec)[quad] = srcr[quad];
+    reinterpret_cast<real4 *>(L.q0)[to] = reinterpret_cast<const real4 *>(L.q0)[from];
+    reinterpret_cast<real4 *>(L.q1)[to] = reinterpret_cast<const real4 *>(L.q1)[from];
+    L.dH[to] = L.dH[from];
+    L.p[to] = L.p[from];
   }
   __syncthreads();
   residual_tile<real, D, RowsPerThread<real, D>::value>(ne, L);
@@ -1347,11 +1357,11 @@ static const void *sbp_fn(bool fp64) {
               : reinterpret_cast<const void *>(&sbp_stage_kernel<float>);
 }
 
-// Workgroups of the stage kernel (the DG-SBP kernel with sbp) that stay resident on the
-// whole device.
-hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile, size_t lds_bytes,
-                            int block, int *out) {
-  int dev = 0, ncu = 0, per_cu = 0;
+// Workgroups of the per-stage or multi-stage kernel (the DG-SBP kernel with sbp) that stay
+// resident on the whole device with lds_bytes of dynamic LDS each.
+hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile, bool multi,
+                            size_t lds_bytes, int block, int *out) {
+  int dev = 0, ncu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1361,25 +1371,21 @@ hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int
   // blocks only start when others finish (for a multi-stage launch, which needs every
   // workgroup resident at once, their neighbours then wait for stages that cannot come).
   // So cap it with 1 KiB granules of the CU's LDS, counting the kernel's own static LDS
-  // (the multi-stage build's workgroup reduction) on top of the dynamic request.  Both
-  // launch kinds use the same grid: the smaller residency of the two builds.
+  // (the multi-stage build's workgroup reduction) on top of the dynamic request.
   int lds_cu = 0;
   e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
   if (e != hipSuccess) return e;
-  for (int multi = 0; multi < 2; ++multi) {
-    const void *fn = sbp ? sbp_fn(fp64) : stage_fn(fp64, cm, wadg, multi != 0, v1, kind, tile);
-    int n = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, lds_bytes);
-    if (e != hipSuccess) return e;
-    hipFuncAttributes fa{};
-    e = hipFuncGetAttributes(&fa, fn);
-    if (e != hipSuccess) return e;
-    const size_t granule = 1024, total = lds_bytes + fa.sharedSizeBytes;
-    const size_t need = (total + granule - 1) / granule * granule;
-    if (need > 0 && lds_cu > 0) n = std::min<long long>(n, (long long)(size_t(lds_cu) / need));
-    per_cu = multi ? std::min(per_cu, n) : n;
-  }
-  *out = ncu * (per_cu > 0 ? per_cu : 1);
+  const void *fn = sbp ? sbp_fn(fp64) : stage_fn(fp64, cm, wadg, multi, v1, kind, tile);
+  int n = 0;
+  e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, lds_bytes);
+  if (e != hipSuccess) return e;
+  hipFuncAttributes fa{};
+  e = hipFuncGetAttributes(&fa, fn);
+  if (e != hipSuccess) return e;
+  const size_t granule = 1024, total = lds_bytes + fa.sharedSizeBytes;
+  const size_t need = (total + granule - 1) / granule * granule;
+  if (need > 0 && lds_cu > 0) n = std::min<long long>(n, (long long)(size_t(lds_cu) / need));
+  *out = ncu * (n > 0 ? n : 1);
   return hipSuccess;
 }
 

@@ -25,8 +25,8 @@ hipError_t launch_stage(bool fp64, bool sbp, const StageArgs &a, int max_blocks,
                         hipStream_t stream);
 hipError_t launch_stage_fused(bool fp64, const StageArgs &a, int max_blocks, size_t lds_bytes, int block,
                               bool cooperative, hipStream_t stream);
-hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile, size_t lds_bytes,
-                            int block, int *out);
+hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile, bool multi,
+                            size_t lds_bytes, int block, int *out);
 int stage_grid(int ntiles, int max_blocks);
 hipError_t launch_diag(bool fp64, const DiagArgs &a, hipStream_t stream);
 hipError_t launch_rest_depth(bool fp64, const DiagArgs &a, hipStream_t stream);
@@ -96,7 +96,7 @@ int default_epb(int D, size_t word, bool wadg, int P, int block) {
   int best = 1;
   for (int E = 1; E <= 64; E *= 2) {
     if (E * dim_Nh(D) > 2 * block) break;
-    if (size_t(tile_words(D, E, wadg, P)) * word > size_t(40 * 1024) * block / kBlock) break;
+    if (size_t(limit_words(D, E, wadg, P)) * word > size_t(40 * 1024) * block / kBlock) break;
     best = E;
   }
   return best;
@@ -151,14 +151,19 @@ struct esdg_swe {
   bool balanced = false;           // mixed degrees: cost-balanced tile ranges uploaded
   size_t ws_bytes = 0;
   std::map<int, int> epb;          // elements per workgroup per element kind
-  size_t lds_bytes = 0;
+  size_t lds_bytes = 0;            // dynamic LDS of a workgroup
+  size_t limit_bytes = 0;          // the tile limit's count of it (limit_words in device_types.hpp)
   int block = kBlock;              // stage-kernel workgroup size (kBlockWide if every kind is wide)
   int kind = 0;                    // the one element kind of every instance (modal), else 0
   int tile = 0;                    // its elements per tile
   bool cooperative = true;         // multi-stage launches through hipLaunchCooperativeKernel (false
                                    // once the residency probe at bind saw the whole grid resident)
   int ref_max = 0;                 // LDS words reserved for the largest reference block
-  int max_blocks = 0;              // resident workgroups of the stage kernel (set at bind)
+  int max_blocks = 0;              // resident workgroups of the per-stage kernel (set at bind)
+  int multi_blocks = 0;            // and of a multi-stage grid, each workgroup counted with the
+                                   // LDS of the tile limit: the plan of a step call, and what
+                                   // esdg_swe_launch_info reports, follow from the tile sizes
+                                   // and not from how much of that the kernels come to use
   std::vector<Tile> tiles;
   std::vector<int> tile_begin, tile_count;
   std::vector<InstDesc> desc;
@@ -497,7 +502,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     s->block = all_wide ? kBlockWide : kBlock;
   }
   // elements per workgroup and LDS: the largest reference block + the largest tile
-  size_t tile = 0;
+  size_t tile = 0, limit = 0;
   for (auto &kv : s->refs) {
     const int D = kv.first, N = key_N(D);
     int shape = opt->tile_shape[N] ? opt->tile_shape[N] : default_shape(D, s->fp64);
@@ -513,7 +518,8 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     s->epb[D] = E;
     if (D == s->kind) s->tile = E;
     s->ref_max = std::max(s->ref_max, ref_words(D));
-    tile = std::max(tile, size_t(tile_words(D, E, s->wadg, P)));
+    tile = std::max(tile, size_t(tile_words(D, E, s->wadg)));
+    limit = std::max(limit, size_t(limit_words(D, E, s->wadg, P)));
   }
   if (s->shapes && (s->contraction != 0 || s->v1)) {
     g_init_error = "esdg_swe_init: tile shapes other than the default need matrix_cores 0 or 1, FP64 or FP32 "
@@ -521,12 +527,12 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     return ESDG_EINVAL;
   }
   s->ref_max = (s->ref_max + 3) & ~3;
-  size_t lds = (size_t(s->ref_max) + tile) * s->word;
-  if (lds > 160 * 1024) {
+  s->limit_bytes = (size_t(s->ref_max) + limit) * s->word;
+  if (s->limit_bytes > 160 * 1024) {
     g_init_error = "esdg_swe_init: elems_per_block needs more than 160 KiB of LDS";
     return ESDG_EINVAL;
   }
-  s->lds_bytes = lds;
+  s->lds_bytes = (size_t(s->ref_max) + tile) * s->word;
   // tiles
   s->tile_begin.resize(n_inst);
   s->tile_count.resize(n_inst);
@@ -608,13 +614,16 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     hipError_t e = scratch_address(&s->scratch_dev);
     if (e != hipSuccess) return s->hip_fail(e, "hipGetSymbolAddress (scratch)");
   }
-  if (s->lds_bytes > 64 * 1024) {
-    hipError_t e = set_stage_lds_limit(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, s->lds_bytes);
+  if (s->limit_bytes > 64 * 1024) {
+    hipError_t e = set_stage_lds_limit(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, s->limit_bytes);
     if (e != hipSuccess) return s->hip_fail(e, "hipFuncSetAttribute (LDS)");
   }
   {
-    hipError_t e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, s->lds_bytes, s->block,
-                                    &s->max_blocks);
+    hipError_t e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, false, s->lds_bytes,
+                                    s->block, &s->max_blocks);
+    if (e == hipSuccess)
+      e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, true, s->limit_bytes,
+                           s->block, &s->multi_blocks);
     if (e != hipSuccess) return s->hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (std::getenv("ESDG_SWE_VERBOSE")) {
       std::fprintf(stderr, "esdg_swe: %s, %d threads and LDS %zu B per workgroup, %d resident workgroups, %zu tiles;",
@@ -643,15 +652,11 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     const InstanceHost &H = s->host[i];
     const Offsets &f = s->off[i];
     if (!s->sbp) {
-      // metric factors in tile-blocked order: [4][E][Nh] per tile, from k0 * 4 * Nh
-      const size_t Nh = size_t(dim_Nh(H.key)), plane = size_t(H.K) * Nh;
-      const size_t E = size_t(s->epb[H.key]);
-      std::vector<double> g(size_t(s->tile_count[i]) * E * 4 * Nh, 0.0);
-      for (int t = s->tile_begin[i]; t < s->tile_begin[i] + s->tile_count[i]; ++t) {
-        const size_t k0 = size_t(s->tiles[t].k0), ne = size_t(s->tiles[t].ne);
-        for (size_t c = 0; c < 4; ++c)
-          for (size_t j = 0; j < ne * Nh; ++j) g[k0 * 4 * Nh + c * E * Nh + j] = H.geo[c * plane + k0 * Nh + j];
-      }
+      // metric factors as quads [K][Nh][4]
+      const size_t nodes = size_t(H.K) * dim_Nh(H.key);
+      std::vector<double> g(nodes * 4);
+      for (size_t c = 0; c < 4; ++c)
+        for (size_t j = 0; j < nodes; ++j) g[4 * j + c] = H.geo[c * nodes + j];
       keep.push_back(to_bulk(g, s->fp64));
       if ((st = upload(s, f.geo, keep.back().data(), keep.back().size()))) return st;
     }
@@ -740,7 +745,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
   if ((st = upload(s, s->progress_off, keep.back().data(), keep.back().size()))) return st;
   s->stage_count = 0;
   if (s->opt.fused_steps == 2)
-    s->fused = stage_grid(int(s->tiles.size()), s->max_blocks) >= int(s->tiles.size());
+    s->fused = stage_grid(int(s->tiles.size()), s->multi_blocks) >= int(s->tiles.size());
   if (s->fused) {
     int dev = 0, coop = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -752,7 +757,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
   // mixed degrees: split the tile list into contiguous chunks of equal estimated cost
   std::vector<int32_t> ranges;
   if (s->refs.size() > 1) {
-    const int G = stage_grid(int(s->tiles.size()), s->max_blocks);
+    const int G = stage_grid(int(s->tiles.size()), s->fused ? s->multi_blocks : s->max_blocks);
     std::vector<long long> cum(s->tiles.size() + 1, 0);
     for (size_t t = 0; t < s->tiles.size(); ++t)
       cum[t + 1] = cum[t] + elem_cost(s->host[s->tiles[t].inst].key) * s->tiles[t].ne;
@@ -782,7 +787,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     StageArgs a = base_args(s, -1);
     a.mode = kProbe;
     a.spin_limit = 1 << 17;
-    e = launch_stage_fused(s->fp64, a, s->max_blocks, s->lds_bytes, s->block, false, s->stream);
+    e = launch_stage_fused(s->fp64, a, s->multi_blocks, s->lds_bytes, s->block, false, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return s->hip_fail(e, "residency probe");
     int32_t word[2] = {0, 0};
@@ -790,7 +795,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     if (e == hipSuccess)
       e = hipMemcpy(&word[1], s->dev<int32_t>(s->flag_off) + kProbeWord, sizeof(int32_t), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return s->hip_fail(e, "hipMemcpy (residency probe)");
-    s->cooperative = (word[0] & 4) != 0 || word[1] != stage_grid(int(s->tiles.size()), s->max_blocks);
+    s->cooperative = (word[0] & 4) != 0 || word[1] != stage_grid(int(s->tiles.size()), s->multi_blocks);
     e = hipMemset(s->ws + s->flag_off, 0, 256);
     if (e != hipSuccess) return s->hip_fail(e, "hipMemset (flag)");
     if (std::getenv("ESDG_SWE_VERBOSE"))
@@ -956,13 +961,13 @@ static esdg_status run_steps_fused(esdg_swe *s, int nsteps) {
     a.nbr_idx = s->dev<int32_t>(s->nbr_idx_off);
     a.stage0 = int32_t(s->stage_count);
     a.nstages = 5 * n;
-    a.resident = stage_grid(a.ntiles, s->max_blocks) >= a.ntiles ? 1 : 0;   // one tile per workgroup
+    a.resident = stage_grid(a.ntiles, s->multi_blocks) >= a.ntiles ? 1 : 0;   // one tile per workgroup
     a.spin_limit = 1 << 17;     // polls (each a device-coherent load): tens of ms, above any one stage
     for (int st = 0; st < 5; ++st) {
       a.rk_a5[st] = kRkA[st];
       a.rk_b5[st] = kRkB[st];
     }
-    hipError_t e = launch_stage_fused(s->fp64, a, s->max_blocks, s->lds_bytes, s->block, s->cooperative, s->stream);
+    hipError_t e = launch_stage_fused(s->fp64, a, s->multi_blocks, s->lds_bytes, s->block, s->cooperative, s->stream);
     if (e != hipSuccess) return s->hip_fail(e, "hipLaunchCooperativeKernel (fused steps)");
     s->stage_count += 5LL * n;
     if (n & 1) s->parity = 1 - s->parity;
@@ -1077,9 +1082,9 @@ esdg_status esdg_swe_launch_info(const esdg_swe *s, int32_t *out4) {
   if (!s->bound) return ESDG_ESTATE;
   const int ntiles = int(s->tiles.size());
   out4[0] = ntiles;
-  out4[1] = s->max_blocks;
+  out4[1] = s->multi_blocks;
   out4[2] = int32_t(s->lds_bytes);
-  out4[3] = !s->fused ? 0 : (stage_grid(ntiles, s->max_blocks) >= ntiles ? 2 : 1);
+  out4[3] = !s->fused ? 0 : (stage_grid(ntiles, s->multi_blocks) >= ntiles ? 2 : 1);
   return ESDG_OK;
 }
 
