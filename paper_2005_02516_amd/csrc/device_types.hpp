@@ -15,6 +15,11 @@ constexpr int kBlockWide = 512;    // stage-kernel workgroups of launches whose 
 // loads and q1 is copied straight from HBM), and the scalars dH and p = gh/2 ([E][Nh] each).
 constexpr int kNodeQuads = 2;
 constexpr int kProbeWord = 16;     // int32 word of the flag block counting a residency probe
+// int32 words from one tile's progress count to the next: each has a 128-byte line of its own,
+// shared by its writer and its pollers alone (packed 32 to a line, the resident launch at
+// N = 1, K = 8192 took 7.1 us a stage instead of 4.9).
+constexpr int kProgressStride = 32;
+
 constexpr int kXcds = 8;           // MI355X accelerator complex dies (each with its own L2)
 
 // Push-target flag: the face node lies on a reflective wall (Section 2.9); its projection
@@ -207,7 +212,7 @@ struct StageArgs {
   // starting at global stage index stage0, buffers alternating from in_buf, coefficients
   // rk_a5/rk_b5[stage mod 5].  Before a stage, a tile waits until every tile holding a face
   // neighbour has completed the previous one; after it, it publishes its count.
-  int32_t *progress;      // [ntiles] stages completed by each tile (monotone over launches)
+  int32_t *progress;      // [ntiles][kProgressStride] stages completed by each tile (monotone over launches)
   const int32_t *nbr_off; // [ntiles + 1] CSR offsets into nbr_idx
   const int32_t *nbr_idx; // tiles (other than itself) holding a face neighbour of each tile
   int32_t stage0, nstages;

@@ -272,12 +272,6 @@ struct StageRun {
   double rk_a, rk_b;
 };
 
-// Stage flags of a multi-stage launch whose tiles stay in LDS (StageArgs::resident).
-constexpr int kResident = 1;       // the tile's records, metric factors, static block, state and
-                                   // RK register stay in LDS between the stages of the launch
-constexpr int kResMid = 2;         // not the first stage: only the neighbour values are fetched
-constexpr int kResLast = 4;        // last stage: the state, RK register and u~ go to HBM
-
 // Weight-adjusted inverse of the curved mass matrix (the implementation remark after eq.
 // (dgform) in Section 2.8): (M_h^k)^{-1} y ~ M^{-1} M_{1/J} M^{-1} y with M_{1/J} =
 // V_q^T W diag(1/J) V_q; the reference mass matrix M is the identity for the orthonormal
@@ -345,8 +339,7 @@ __device__ __forceinline__ void minv_rows(const LT &L, const real *X, F store) {
 // float it has the relative accuracy of the depth itself where the water is shallow).
 template <typename real, int N, int CM, bool WADG, class LT>
 __device__ __forceinline__ void project_tile(const InstDesc &d, int k0, int ne, LT &L, real *out,
-                                             real *nbx_out, int32_t *flag, bool coherent, int res = 0) {
-  const bool to_records = (res & kResident) && !(res & kResLast);
+                                             real *nbx_out, int32_t *flag, bool coherent, bool to_records = false) {
   constexpr int Np = dim_Np(N), Nq = dim_Nq(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N);
   const double g = d.g;
   const int tid = phase_tid(), nth = threads<LT>();
@@ -737,13 +730,33 @@ __device__ __forceinline__ bool wait_neighbours(const StageArgs &a, int t, int t
     for (int j = b + int(threadIdx.x); j < e; j += 64) {
       const int u = read_const(a.nbr_idx, j);
       int spins = 0;
-      while (__hip_atomic_load(a.progress + u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+      while (__hip_atomic_load(a.progress + u * kProgressStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
         if (++spins > a.spin_limit) { ok = 0; break; }
         __builtin_amdgcn_s_sleep(1);
       }
     }
   }
   return __syncthreads_and(ok) != 0;
+}
+
+// The same wait for a resident tile, whose caller puts the barrier: false, with flag bit 1 set,
+// once a wait has given up (`waits` false: do not wait).  Wave 0 only.
+__device__ __forceinline__ bool poll_neighbours(const StageArgs &a, int t, int target, bool waits) {
+  bool ok = waits;
+  if (waits && threadIdx.x < 64) {
+    const int b = read_const(a.nbr_off, t), e = read_const(a.nbr_off, t + 1);
+    for (int j = b + int(threadIdx.x); j < e; j += 64) {
+      const int u = read_const(a.nbr_idx, j);
+      int spins = 0;
+      while (__hip_atomic_load(a.progress + u * kProgressStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        if (++spins > a.spin_limit) { ok = false; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+    }
+    if (!ok) atomicOr(a.flag, 2);
+    ok = __all(ok);
+  }
+  return ok;
 }
 
 // After a stage of tile t: every wave waits until its stores have completed (the pushed
@@ -753,20 +766,49 @@ __device__ __forceinline__ bool wait_neighbours(const StageArgs &a, int t, int t
 __device__ __forceinline__ void publish(const StageArgs &a, int t, int value) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(a.progress + t, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) __hip_atomic_store(a.progress + t * kProgressStride, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Four values through device-coherent 16-byte loads (the workgroup that stored them may sit on
+// another XCD); each asm block waits for what it loads.
+__device__ __forceinline__ void load_coherent(const float *p, float *v) {
+  f32x4_t x;
+  asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(x) : "v"(p) : "memory");
+  v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
+}
+__device__ __forceinline__ void load_coherent(const double *p, double *v) {
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
+  f64x2_t x, y;
+  asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %2, off offset:16 sc1\n\ts_waitcnt vmcnt(0)"
+               : "=&v"(x), "=&v"(y) : "v"(p) : "memory");
+  v[0] = x[0]; v[1] = x[1]; v[2] = y[0]; v[3] = y[1];
+}
+
+// Neighbour values as fetch_tile left them in LDS.
+template <typename real, class LT>
+__device__ __forceinline__ auto fetched_neighbours(const LT &L) {
+  const real *nb = L.nb;
+  return [nb](int i, real *v) {
+    typedef real real4 __attribute__((ext_vector_type(4)));
+    const real4 x = reinterpret_cast<const real4 *>(nb)[i];
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+  };
 }
 
 // Phase 3: interface terms of the face rows (Section 2.8): W_f [ nJ . f_S(u~, u~+) + 1/2 g h
-// (H+ - Href) nJ ] - LF penalty, one task per (element, face node), written over the
-// neighbour values they are formed from (the lift adds them).  A pass of its own so that a
+// (H+ - Href) nJ ] - LF penalty, one task per (element, face node), into the first three words
+// of the node's four in the neighbour block (the lift adds them).  A pass of its own so that a
 // resident tile can run the whole pair loop before it waits for its neighbours' values.
-template <typename real, int N, class LT>
-__device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L) {
+// neighbour(i, v): h, u, v, H - Href on the other side of face node i.
+template <typename real, int N, class LT, class FN>
+__device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L, FN neighbour) {
   constexpr int Nq = dim_Nq(N), Nfq = dim_Nfq(N);
   for (int i = phase_tid(); i < ne * Nfq; i += threads<LT>()) {
     const int e = int(unsigned(i) / unsigned(Nfq)), f = i - __umul24(unsigned(e), unsigned(Nfq));
     real t0, t1, t2;
-    interface_terms<real>(L, __umul24(unsigned(e), unsigned(dim_Nh(N))) + Nq + f, L.nb + 4 * i, L.wf[f], L.nr[f], L.ns[f],
+    real nbp[4];
+    neighbour(i, nbp);
+    interface_terms<real>(L, __umul24(unsigned(e), unsigned(dim_Nh(N))) + Nq + f, nbp, L.wf[f], L.nr[f], L.ns[f],
                           real(d.g), d.flux, t0, t1, t2);
     L.nb[4 * i] = t0;
     L.nb[4 * i + 1] = t1;
@@ -774,68 +816,23 @@ __device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L)
   }
 }
 
-template <typename real, int N, int CM, bool WADG, bool MULTI, int EC, int NT>
-__device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r, const InstDesc &d, int index, int k0,
-                                           int ne, real *sm, real *tile, int res = 0, int t = 0, int target = 0) {
-  constexpr int Np = dim_Np(N), Nh = dim_Nh(N), Nfq = dim_Nfq(N);
-  typedef Lds<real, N, EC, NT> LT;
-  const int tid = phase_tid(), nth = threads<LT>();
-  LT L(sm, tile, d.E, mass_words(N, WADG));
-  const int E = L.E;
-  const real g = real(d.g);
-  const bool mid = res & kResMid;                // resident tile after its first stage
-  const bool keep = (res & kResident) && !(res & kResLast);   // state stays in LDS only
-  // The multi-stage build runs only multi-stage launches (and their residency probe, which
-  // returns before any tile): RK stages on the instance buffers.  Taking that as given here
-  // compiles the projection-only and RHS paths and the external buffers out of it, whose
-  // addresses would otherwise stay live in scalar registers (and spill) across the stage.
-  const int mode = MULTI ? int(kStage) : r.mode;
-  // a resident tile after its first stage has everything but the neighbour values in LDS;
-  // it fetches those after the pair loop, once its neighbours have pushed them
-  if (!mid) fetch_tile<real, N, WADG, MULTI, EC>(a, r, d, index, k0, ne, L);
-  if (!MULTI && mode == kProject) {
-    __syncthreads();
-    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(a.ext_ut ? a.ext_ut : d.ut[r.out_buf]),
-                              static_cast<real *>(a.ext_nbx ? a.ext_nbx : d.nbx[r.out_buf]), a.flag,
-                              MULTI && a.progress != nullptr);
-    return true;
-  }
-  // a resident tile after its first stage skips the fetch and the records: what its residual
-  // reads (the node records) was written before the barrier of the previous stage's publish
-  if (!mid) __syncthreads();
-  // phase 1: node records from the fetched u~ (a resident tile's previous projection wrote
-  // them directly)
-  for (int i = tid; i < ne * Nh && !mid; i += nth)
-    write_record<real>(L, i, L.raw[i], L.raw[E * Nh + i], L.raw[2 * E * Nh + i], L.raw[3 * E * Nh + i], g);
-  if (!mid) __syncthreads();
-  residual_tile<real, N, RowsPerThread<real, N>::value>(ne, L);
-  if (!mid) {
-    interface_tile<real, N>(d, ne, L);
-  } else {
-    if (!wait_neighbours(a, t, target)) return false;
-    // from here to its publish the tile is on its neighbours' critical path (their next
-    // stage waits for its pushes), while the other workgroups on the CU that are still in
-    // their pair loop have slack: raise this workgroup's wave priority until the publish
-    __builtin_amdgcn_s_setprio(2);
-    copy_block<LT, EC * Nfq * 4 * int(sizeof(real)), true>(
-        L.nb, static_cast<const real *>(d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4, ne * Nfq * 4 * int(sizeof(real)));
-    wait_copies();
-  }
-  if (mid) {
-    __syncthreads();
-    interface_tile<real, N>(d, ne, L);
-  }
-  __syncthreads();
+// From the residual and interface terms to the updated state: the lift, the mass inverse and
+// (mode kStage) the LSRK update, or (kRhs) the right-hand side.  write: the state and RK
+// register go to HBM too.  Elements beyond a ragged tile's ne are dropped.
+template <typename real, int N, int CM, bool WADG, class LT>
+__device__ __forceinline__ void lift_update(const StageArgs &a, const StageRun &r, const InstDesc &d, int mode, int k0,
+                                            int ne, LT &L, bool write) {
+  constexpr int Np = dim_Np(N), Nh = dim_Nh(N);
+  const int E = L.E, nth = threads<LT>();
   // lift: y = V_h^T r_h
-  contract<CM, Np, Nh, Np, true, real>(L.Vh, 3 * E, threads<LT>() >> 6, residual_in<real, N>(L), cols_out<Np>(L.T));
+  contract<CM, Np, Nh, Np, true, real>(L.Vh, 3 * E, nth >> 6, residual_in<real, N>(L), cols_out<Np>(L.T));
   __syncthreads();
   // rhs = -Minv y; store it, or do the LSRK update
   const size_t splane = size_t(d.K) * Np;
   real *uh = static_cast<real *>(d.uh);
   real *du = static_cast<real *>(d.du);
-  real *rhs_out = static_cast<real *>(MULTI ? nullptr : a.ext_rhs);
   const real ra = real(r.rk_a), rdt = real(d.dt), rb = real(r.rk_b);
-  // one output per (field, element, mode); elements beyond a ragged tile's ne are dropped
+  // one output per (field, element, mode)
   auto update = [&](int i, real y) {
     const real rr = -y;
     const FieldTask<Np> k(i, E * Np);
@@ -843,11 +840,11 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r
     const size_t o = size_t(unsigned(k.c)) * splane + size_t(k0) * Np + unsigned(k.r);
     const bool in = k.r < ne * Np;
     if (mode == kRhs) {
-      if (in) rhs_out[o] = rr;
+      if (in) static_cast<real *>(a.ext_rhs)[o] = rr;
     } else {
       const real dn = ra * L.DU[i] + rdt * rr;
       const real un = L.U[i] + rb * dn;
-      if (!keep && in) {
+      if (write && in) {
         du[o] = dn;
         uh[o] = un;
       }
@@ -860,19 +857,107 @@ __device__ __forceinline__ bool stage_tile(const StageArgs &a, const StageRun &r
     __syncthreads();
     wadg_second<real, N>(L, L.R, L.T);
     __syncthreads();
-    for (int i = tid; i < 3 * E * Np; i += nth) update(i, L.T[i]);
+    for (int i = phase_tid(); i < 3 * E * Np; i += nth) update(i, L.T[i]);
   } else {
     minv_rows<real, N>(L, L.T, update);
   }
-  if (mode == kStage) {
-    __syncthreads();
-    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(d.ut[r.out_buf]),
-                              static_cast<real *>(d.nbx[r.out_buf]), a.flag, MULTI && a.progress != nullptr, res);
-  }
-  return true;
 }
 
+// One stage (or projection, or right-hand side) of a tile that is fetched for it.
+template <typename real, int N, int CM, bool WADG, bool MULTI, int EC, int NT>
+__device__ __forceinline__ void stage_tile(const StageArgs &a, const StageRun &r, const InstDesc &d, int index, int k0,
+                                           int ne, real *sm, real *tile) {
+  constexpr int Nh = dim_Nh(N);
+  typedef Lds<real, N, EC, NT> LT;
+  const int tid = phase_tid(), nth = threads<LT>();
+  LT L(sm, tile, d.E, mass_words(N, WADG));
+  const int E = L.E;
+  // The multi-stage build runs only multi-stage launches (and their residency probe, which
+  // returns before any tile): RK stages on the instance buffers.  Taking that as given here
+  // compiles the projection-only and RHS paths and the external buffers out of it, whose
+  // addresses would otherwise stay live in scalar registers (and spill) across the stage.
+  const int mode = MULTI ? int(kStage) : r.mode;
+  fetch_tile<real, N, WADG, MULTI, EC>(a, r, d, index, k0, ne, L);
+  __syncthreads();
+  if (!MULTI && mode == kProject) {
+    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(a.ext_ut ? a.ext_ut : d.ut[r.out_buf]),
+                                    static_cast<real *>(a.ext_nbx ? a.ext_nbx : d.nbx[r.out_buf]), a.flag, false);
+    return;
+  }
+  // phase 1: node records from the fetched u~
+  const real g = real(d.g);
+  for (int i = tid; i < ne * Nh; i += nth)
+    write_record<real>(L, i, L.raw[i], L.raw[E * Nh + i], L.raw[2 * E * Nh + i], L.raw[3 * E * Nh + i], g);
+  __syncthreads();
+  residual_tile<real, N, RowsPerThread<real, N>::value>(ne, L);
+  interface_tile<real, N>(d, ne, L, fetched_neighbours<real>(L));
+  __syncthreads();
+  lift_update<real, N, CM, WADG>(a, r, d, mode, k0, ne, L, true);
+  if (mode == kStage) {
+    __syncthreads();
+    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(d.ut[r.out_buf]), static_cast<real *>(d.nbx[r.out_buf]),
+                                    a.flag, MULTI);
+  }
+}
 
+// All stages of a multi-stage launch for a tile that stays in LDS: its records, metric
+// factors, static block, state and RK register are fetched once, each projection writes the
+// next stage's records, and only the last stage writes the state, RK register and u~ back.
+// Between stages the tile waits for its face neighbours after its pair loop and reads their
+// pushed values straight into the interface terms.  A wait that gives up sets flag bit 1;
+// the workgroup then goes on without waiting any more (the state is undefined and the flag
+// reports it), so every workgroup ends.
+// Bound by the chain of its short phases, then by the neighbours' skew.  Measured per stage,
+// before (one stage body for all launches, counts packed 32 to a line) and now: FP32 N = 3,
+// K = 8192 8.66 -> 7.33 us, N = 2 K = 8192 7.3 -> 6.3, N = 1 K = 8192 6.05 -> 4.91, FP64
+// N = 2 K = 8192 10.05 -> 8.65; with packed counts this loop alone made N = 1 7.1 us (each
+// publish took its line from all the pollers of 32 tiles).
+template <typename real, int N, int CM, bool WADG, int EC, int NT>
+__device__ __forceinline__ void resident_tile(const StageArgs &a, const InstDesc &d, int t, int index, int k0, int ne,
+                                              real *sm, real *tile) {
+  constexpr int Nh = dim_Nh(N), Nfq = dim_Nfq(N);
+  typedef Lds<real, N, EC, NT> LT;
+  LT L(sm, tile, d.E, mass_words(N, WADG));
+  const int E = L.E, nth = threads<LT>();
+  const real g = real(d.g);
+  StageRun r{kStage, a.in_buf, 1 - a.in_buf, 0.0, 0.0};
+  fetch_tile<real, N, WADG, true, EC>(a, r, d, index, k0, ne, L);
+  __syncthreads();
+  for (int i = phase_tid(); i < ne * Nh; i += nth)
+    write_record<real>(L, i, L.raw[i], L.raw[E * Nh + i], L.raw[2 * E * Nh + i], L.raw[3 * E * Nh + i], g);
+  __syncthreads();
+  bool waits = true;
+#pragma unroll 1
+  for (int s = 0, s5 = 0; s < a.nstages; ++s, s5 = s5 == 4 ? 0 : s5 + 1) {
+    const bool last = s + 1 == a.nstages;
+    r.rk_a = a.rk_a5[s5];
+    r.rk_b = a.rk_b5[s5];
+    residual_tile<real, N, RowsPerThread<real, N>::value>(ne, L);
+    if (s > 0) {
+      waits = poll_neighbours(a, t, a.stage0 + s, waits);
+      __syncthreads();
+      // from here to its publish the tile is on its neighbours' critical path (their next
+      // stage waits for its pushes), while the other workgroups on the CU that are still in
+      // their pair loop have slack: raise this workgroup's wave priority until the publish
+      __builtin_amdgcn_s_setprio(2);
+      const real *nbx = static_cast<const real *>(d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4;
+      interface_tile<real, N>(d, ne, L, [nbx](int i, real *v) {
+        load_coherent(nbx + 4 * size_t(unsigned(i)), v);
+      });
+    } else {
+      interface_tile<real, N>(d, ne, L, fetched_neighbours<real>(L));
+    }
+    __syncthreads();
+    lift_update<real, N, CM, WADG>(a, r, d, kStage, k0, ne, L, last);
+    __syncthreads();
+    project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(d.ut[r.out_buf]), static_cast<real *>(d.nbx[r.out_buf]),
+                                    a.flag, true, !last);
+    publish(a, t, a.stage0 + s + 1);
+    __builtin_amdgcn_s_setprio(0);
+    r.in_buf = r.out_buf;
+    r.out_buf = 1 - r.in_buf;
+  }
+}
 
 // Persistent stage kernel: block b walks a contiguous range of tiles.  Blocks are dealt
 // to the XCDs round-robin, so block b's range is chosen as range number
@@ -934,7 +1019,7 @@ stage_kernel(StageArgs a) {
   // resident: the launch gives this workgroup at most one tile (cost-balanced ranges can
   // still give a workgroup two; that one then re-reads its tiles every stage)
   const bool resident = multi && a.resident && t1 - t0 <= 1;
-  const int nst = multi ? a.nstages : 1;
+  const int nst = !multi ? 1 : resident ? (t1 > t0 ? 1 : 0) : a.nstages;
   int loaded_N = 0;
   for (int s = 0; s < nst; ++s) {
     StageRun r{a.mode, a.in_buf, a.out_buf, a.rk_a, a.rk_b};
@@ -946,10 +1031,7 @@ stage_kernel(StageArgs a) {
       r.rk_b = a.rk_b5[s % 5];
     }
     for (int t = t0; t < t1; ++t) {
-      const int res = resident ? kResident | (s > 0 ? kResMid : 0) | (s == nst - 1 ? kResLast : 0) : 0;
-      // non-resident tiles wait before the stage (they re-read their neighbours' values in
-      // the fetch); resident ones inside it, after their pair loop
-      if (multi && s > 0 && !(res & kResMid) && !wait_neighbours(a, t, a.stage0 + s)) {
+      if (multi && s > 0 && !wait_neighbours(a, t, a.stage0 + s)) {
         if (threadIdx.x == 0) atomicOr(a.flag, 2);
         return;
       }
@@ -962,9 +1044,11 @@ stage_kernel(StageArgs a) {
         copy_block<Threads<NT>, words * int(sizeof(real))>(sm, d.ref, ((ref_words(d.N) + 3) & ~3) * int(sizeof(real)));
         loaded_N = KIND != 0 ? KIND : d.N;
       }
-      bool ok = true;
-#define ESDG_STAGE_CASE(D) \
-  case D: ok = stage_tile<real, D, CM, WADG, MULTI, EC, NT>(a, r, d, tl.index, tl.k0, tl.ne, sm, tile, res, t, a.stage0 + s); break;
+#define ESDG_STAGE_CASE(D)                                                                                     \
+  case D:                                                                                                      \
+    if (MULTI && resident) resident_tile<real, D, CM, WADG, EC, NT>(a, d, t, tl.index, tl.k0, tl.ne, sm, tile); \
+    else stage_tile<real, D, CM, WADG, MULTI, EC, NT>(a, r, d, tl.index, tl.k0, tl.ne, sm, tile);               \
+    break;
       if constexpr (KIND != 0) {     // every tile is of this kind (the host's choice of kernel)
         switch (KIND) {
           ESDG_STAGE_CASE(KIND)
@@ -983,14 +1067,7 @@ stage_kernel(StageArgs a) {
         }
       }
 #undef ESDG_STAGE_CASE
-      if (!ok) {
-        if (threadIdx.x == 0) atomicOr(a.flag, 2);
-        return;
-      }
-      if (multi) {
-        publish(a, t, a.stage0 + s + 1);
-        __builtin_amdgcn_s_setprio(0);
-      }
+      if (multi && !resident) publish(a, t, a.stage0 + s + 1);
       else __syncthreads();
     }
   }
@@ -1217,7 +1294,7 @@ __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, 
   }
   __syncthreads();
   residual_tile<real, D, RowsPerThread<real, D>::value>(ne, L);
-  interface_tile<real, D>(d, ne, L);
+  interface_tile<real, D>(d, ne, L, fetched_neighbours<real>(L));
   __syncthreads();
   // du/dt = -(W J)^{-1} [I; I_f]^T r_h; store it, or do the LSRK update
   real *uh = static_cast<real *>(d.uh);

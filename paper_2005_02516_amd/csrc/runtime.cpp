@@ -291,7 +291,7 @@ esdg_status check_flag(esdg_swe *s) {
     (void)hipMemcpy(s->dev<int32_t>(s->flag_off), &zero, sizeof zero, hipMemcpyHostToDevice);
     if (flag & 2) {
       // a fused launch gave up waiting: restart the stage counts from zero
-      std::vector<int32_t> z(s->tiles.size(), 0);
+      std::vector<int32_t> z(s->tiles.size() * kProgressStride, 0);
       (void)hipMemcpy(s->dev<int32_t>(s->progress_off), z.data(), z.size() * sizeof(int32_t), hipMemcpyHostToDevice);
       s->stage_count = 0;
       return s->fail(ESDG_EDEVICE, "fused step: a tile's wait for its neighbours gave up; the state is undefined");
@@ -593,7 +593,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
   s->flag_off = take(256);
   s->partial_off = take(s->tiles.size() * 6 * sizeof(double));
   s->ranges_off = take((s->tiles.size() + 16) * sizeof(int32_t));
-  s->progress_off = take(s->tiles.size() * sizeof(int32_t));
+  s->progress_off = take(s->tiles.size() * kProgressStride * sizeof(int32_t));
   s->nbr_off_off = take(s->nbr_off.size() * sizeof(int32_t));
   s->nbr_idx_off = take(std::max<size_t>(s->nbr_idx.size(), 1) * sizeof(int32_t));
   s->ws_bytes = o;
@@ -741,7 +741,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
   if ((st = upload(s, s->nbr_off_off, s->nbr_off.data(), s->nbr_off.size() * sizeof(int32_t)))) return st;
   if (!s->nbr_idx.empty() && (st = upload(s, s->nbr_idx_off, s->nbr_idx.data(), s->nbr_idx.size() * sizeof(int32_t))))
     return st;
-  keep.push_back(std::vector<unsigned char>(s->tiles.size() * sizeof(int32_t), 0));
+  keep.push_back(std::vector<unsigned char>(s->tiles.size() * kProgressStride * sizeof(int32_t), 0));
   if ((st = upload(s, s->progress_off, keep.back().data(), keep.back().size()))) return st;
   s->stage_count = 0;
   if (s->opt.fused_steps == 2)
@@ -945,7 +945,7 @@ static esdg_status run_steps_fused(esdg_swe *s, int nsteps) {
   for (int done = 0; done < nsteps;) {
     const int n = std::min(nsteps - done, 1 << 20);
     if (s->stage_count + 5LL * n >= (1LL << 31) - 1) {
-      std::vector<int32_t> z(s->tiles.size(), 0);
+      std::vector<int32_t> z(s->tiles.size() * kProgressStride, 0);
       hipError_t e = hipMemcpyAsync(s->dev<int32_t>(s->progress_off), z.data(), z.size() * sizeof(int32_t),
                                     hipMemcpyHostToDevice, s->stream);
       if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
