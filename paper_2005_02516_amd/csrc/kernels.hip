@@ -262,8 +262,18 @@ template <> struct RowsPerThread<float, make_key(1, 2)> { static constexpr int v
 template <> struct RowsPerThread<float, make_key(3, 2)> { static constexpr int value = 2; };   // 18 + 12
 // The tile size the single-kind kernel of a kind is built for (0: none).
 template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) {
-  return sizeof(real) == 4 ? (kind == 1 ? 32 : kind == 2 ? 14 : kind == 3 ? 8 : kind == 4 ? 5 : kind == 5 ? 7 : 0)
-                           : (kind == 1 ? 16 : kind == 2 ? 7 : kind == 3 ? 4 : kind == 4 ? 5 : kind == 5 ? 7 : 0);
+  const bool f = sizeof(real) == 4;
+  switch (kind) {
+    case 1: return f ? 32 : 16;
+    case 2: return f ? 14 : 7;
+    case 3: return f ? 8 : 4;
+    case 4: return 5;
+    case 5: return 7;
+    case make_key(1, 2): return f ? 16 : 8;
+    case make_key(2, 2): return f ? 13 : 8;
+    case make_key(3, 2): case make_key(4, 2): return f ? 8 : 4;
+    default: return 0;
+  }
 }
 
 // What changes from stage to stage of a launch.
@@ -1178,15 +1188,16 @@ __global__ void __launch_bounds__(kBlock) rest_depth_kernel(DiagArgs a) {
 // folded source, interface terms) evaluated with the face values taken from the volume
 // nodes they coincide with: each face row is added to its volume node's row.
 
-// LDS carve-up of one DG-SBP tile (see tile_words()).
-template <typename real, int D>
+// LDS carve-up of one DG-SBP tile (see tile_words()).  EC: E where the kernel is built for one
+// tile size, else 0.
+template <typename real, int D, int EC>
 struct LdsSbp {
   static constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), NT = kBlock;
   real *ref, *ST, *FT, *wf, *nr, *ns, *fvol, *vface;
   real *q0, *q1, *dH, *p, *R, *nb, *U, *DU, *iwJ, *dep, *geo;
   int32_t *pp;
   int E;
-  __device__ LdsSbp(real *sm, real *tile, int e) : E(e) {
+  __device__ LdsSbp(real *sm, real *tile, int e) : E(EC != 0 ? EC : e) {
     ref = sm;
     ST = ref;
     FT = ST + 2 * Nh * Nq;
@@ -1210,130 +1221,122 @@ struct LdsSbp {
   }
 };
 
-// Face values (h, u, v, H - Href) of the tile's state, pushed into the neighbours' slots (a
-// reflective wall node, Section 2.9, writes the mirror state into its own slot).
-template <typename real, int D>
-__device__ __forceinline__ void sbp_push(const InstDesc &d, int ne, LdsSbp<real, D> &L, real *nbx_out, int32_t *flag) {
+// Face node f of element e (its volume node is entry j of the tile): the values (h, u, v,
+// H - Href) of its state, pushed into the neighbour's slot (a reflective wall node, Section
+// 2.9, writes the mirror state into its own slot).  True for a non-physical state.
+template <typename real, int D, class LT>
+__device__ __forceinline__ bool sbp_push(const LT &L, int e, int f, int j, double eta, double hu, double hv,
+                                         real *nbx_out) {
   constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D);
-  bool bad = false;
-  for (int i = phase_tid(); i < ne * Nfq; i += blockDim.x) {
-    const int e = i / Nfq, f = i - e * Nfq, j = e * Nq + int(L.fvol[f]);
-    const double eta = L.U[j], hu = L.U[L.E * Nq + j], hv = L.U[2 * L.E * Nq + j];
-    const double h = eta + double(L.dep[j]);
-    const double u = hu / h, v = hv / h;
-    double pu = u, pv = v;
-    const uint32_t tgt = uint32_t(L.pp[i]);
-    if (tgt & kPushWall) {
-      const double nr = double(L.nr[f]), ns = double(L.ns[f]);
-      const double nx = double(L.geo[j]) * nr + double(L.geo[L.E * Nq + j]) * ns;
-      const double ny = double(L.geo[2 * L.E * Nq + j]) * nr + double(L.geo[3 * L.E * Nq + j]) * ns;
-      const double c = 2.0 * (u * nx + v * ny) / (nx * nx + ny * ny);
-      pu = u - c * nx;
-      pv = v - c * ny;
-    }
-    typedef real real4 __attribute__((ext_vector_type(4)));
-    const real4 val = {real(h), real(pu), real(pv), real(eta)};
-    *reinterpret_cast<real4 *>(nbx_out + size_t(tgt & ~kPushWall) * 4) = val;
-    bad |= bad_value(h, hu, hv);
+  typedef real real4 __attribute__((ext_vector_type(4)));
+  const double h = eta + double(L.dep[j]);
+  const double u = hu / h, v = hv / h;
+  double pu = u, pv = v;
+  const uint32_t tgt = uint32_t(L.pp[__umul24(unsigned(e), unsigned(Nfq)) + f]);
+  if (tgt & kPushWall) {
+    const double nr = double(L.nr[f]), ns = double(L.ns[f]);
+    const double nx = double(L.geo[j]) * nr + double(L.geo[L.E * Nq + j]) * ns;
+    const double ny = double(L.geo[2 * L.E * Nq + j]) * nr + double(L.geo[3 * L.E * Nq + j]) * ns;
+    const double c = 2.0 * (u * nx + v * ny) / (nx * nx + ny * ny);
+    pu = u - c * nx;
+    pv = v - c * ny;
   }
-  if (bad) atomicOr(flag, 1);
+  *reinterpret_cast<real4 *>(nbx_out + size_t(tgt & ~kPushWall) * 4) = real4{real(h), real(pu), real(pv), real(eta)};
+  return bad_value(h, hu, hv);
 }
 
-template <typename real, int D>
+// One DG-SBP tile: fetch, node records, residual and interface terms, then one task per volume
+// node for the update and, at a boundary node, its push.  Bound by the chain of those phases
+// and the pair loop's vector work.  Measured per stage with one kernel for all degrees and
+// tile sizes, records and pushes in phases of their own, and now: FP32 K = 32768 N = 1..4
+// 17.7, 28, 41.6, 54 -> 14.9, 20.3, 34, 49 us; FP64 N = 4, K = 8192 30 -> 25.6.
+template <typename real, int D, int EC>
 __device__ __forceinline__ void sbp_tile(const StageArgs &a, const InstDesc &d, int index, int k0, int ne, real *sm,
                                          real *tile) {
   constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D), SW = stat_words(D);
-  LdsSbp<real, D> L(sm, tile, d.E);
+  typedef LdsSbp<real, D, EC> LT;
+  typedef real real4 __attribute__((ext_vector_type(4)));
+  LT L(sm, tile, d.E);
   const int E = L.E;
   const int tid = phase_tid(), nth = kBlock;
   const size_t splane = size_t(d.K) * Nq;
-  typedef LdsSbp<real, D> LT;
   // fetch: state, RK register, static block, neighbour values
-  copy_state<LT, Nq, 0>(L.U, a.ext_state ? a.ext_state : d.uh, splane, k0, ne, E);
-  if (a.mode == kStage) copy_state<LT, Nq, 0>(L.DU, d.du, splane, k0, ne, E);
-  copy_block<LT, 0>(L.iwJ, static_cast<const real *>(d.stat) + size_t(index) * stat_tile(D, E, false),
-                    E * SW * int(sizeof(real)));
+  copy_state<LT, Nq, EC>(L.U, a.ext_state ? a.ext_state : d.uh, splane, k0, ne, E);
+  if (a.mode == kStage) copy_state<LT, Nq, EC>(L.DU, d.du, splane, k0, ne, E);
+  copy_block<LT, EC * SW * int(sizeof(real))>(L.iwJ, static_cast<const real *>(d.stat) + size_t(index) * stat_tile(D, E, false),
+                                              E * SW * int(sizeof(real)));
   if (a.mode != kProject) {
     const real *nbx = static_cast<const real *>(a.ext_nbx ? a.ext_nbx : d.nbx[a.in_buf]) + size_t(k0) * Nfq * 4;
-    copy_block<LT, 0>(L.nb, nbx, ne * Nfq * 4 * int(sizeof(real)));
+    copy_block<LT, EC * Nfq * 4 * int(sizeof(real))>(L.nb, nbx, ne * Nfq * 4 * int(sizeof(real)));
   }
   wait_copies();
   __syncthreads();
   real *nbx_out = static_cast<real *>(a.ext_nbx ? a.ext_nbx : d.nbx[a.out_buf]);
+  bool bad = false;
   if (a.mode == kProject) {
-    sbp_push<real, D>(d, ne, L, nbx_out, a.flag);
+    for (int i = tid; i < ne * Nfq; i += nth) {
+      const int e = int(unsigned(i) / unsigned(Nfq)), f = i - e * Nfq, j = e * Nq + int(L.fvol[f]);
+      bad |= sbp_push<real, D>(L, e, f, j, L.U[j], L.U[E * Nq + j], L.U[2 * E * Nq + j], nbx_out);
+    }
+    if (bad) atomicOr(a.flag, 1);
     return;
   }
-  // node records of the volume nodes, from the nodal state (h in double from eta and the
-  // rest depth; H - Href is eta itself)
+  // node records, from the nodal state (h in double from eta and the rest depth; H - Href is
+  // eta itself); the face nodes' are those of the volume nodes they coincide with
   const real g = real(d.g);
-  bool bad = false;
-  for (int i = tid; i < ne * Nq; i += nth) {
-    const double eta = L.U[i], hu = L.U[E * Nq + i], hv = L.U[2 * E * Nq + i];
-    const double h = eta + double(L.dep[i]);
+  for (int i = tid; i < ne * Nh; i += nth) {
+    const int e = int(unsigned(i) / unsigned(Nh)), n = i - e * Nh, q = n < Nq ? n : int(L.fvol[n - Nq]);
+    const int j = e * Nq + q;
+    const double eta = L.U[j], hu = L.U[E * Nq + j], hv = L.U[2 * E * Nq + j];
+    const double h = eta + double(L.dep[j]);
     const double u = hu / h, v = hv / h;
-    const int e = i / Nq, q = i - e * Nq;
-    typedef real real4 __attribute__((ext_vector_type(4)));
-    const int r = e * Nh + q;
-    reinterpret_cast<real4 *>(L.q0)[r] = real4{real(0.5 * hu), real(0.5 * hv), real(0.5 * u), real(0.5 * v)};
-    reinterpret_cast<real4 *>(L.q1)[r] = real4{L.geo[i], L.geo[E * Nq + i], L.geo[2 * E * Nq + i], L.geo[3 * E * Nq + i]};
-    L.dH[r] = real(eta);
-    L.p[r] = real(0.5) * g * real(h);
+    reinterpret_cast<real4 *>(L.q0)[i] = real4{real(0.5 * hu), real(0.5 * hv), real(0.5 * u), real(0.5 * v)};
+    reinterpret_cast<real4 *>(L.q1)[i] = real4{L.geo[j], L.geo[E * Nq + j], L.geo[2 * E * Nq + j], L.geo[3 * E * Nq + j]};
+    L.dH[i] = real(eta);
+    L.p[i] = real(0.5) * g * real(h);
     bad |= bad_value(h, hu, hv);
-  }
-  if (bad) atomicOr(a.flag, 1);
-  __syncthreads();
-  // the face nodes' records are those of the volume nodes they coincide with
-  for (int i = tid; i < ne * Nfq; i += nth) {
-    const int e = i / Nfq, f = i - e * Nfq, to = e * Nh + Nq + f, from = e * Nh + int(L.fvol[f]);
-    typedef real real4 __attribute__((ext_vector_type(4)));
-    reinterpret_cast<real4 *>(L.q0)[to] = reinterpret_cast<const real4 *>(L.q0)[from];
-    reinterpret_cast<real4 *>(L.q1)[to] = reinterpret_cast<const real4 *>(L.q1)[from];
-    L.dH[to] = L.dH[from];
-    L.p[to] = L.p[from];
   }
   __syncthreads();
   residual_tile<real, D, RowsPerThread<real, D>::value>(ne, L);
   interface_tile<real, D>(d, ne, L, fetched_neighbours<real>(L));
   __syncthreads();
-  // du/dt = -(W J)^{-1} [I; I_f]^T r_h; store it, or do the LSRK update
-  real *uh = static_cast<real *>(d.uh);
-  real *du = static_cast<real *>(d.du);
-  real *rhs_out = static_cast<real *>(a.ext_rhs);
+  // du/dt = -(W J)^{-1} [I; I_f]^T r_h; store it, or do the LSRK update and push
   const real ra = real(a.rk_a), rdt = real(d.dt), rb = real(a.rk_b);
-  for (int i = tid; i < 3 * ne * Nq; i += nth) {
-    const int c = (i >= ne * Nq) + (i >= 2 * ne * Nq), j = i - c * ne * Nq, e = j / Nq, n = j - e * Nq;
-    const auto rh = residual_in<real, D>(L)(c * E + e);
-    real r = rh(n, n >> 2);
+  for (int j = tid; j < ne * Nq; j += nth) {
+    const int e = int(unsigned(j) / unsigned(Nq)), n = j - e * Nq;
     const int vf = int(L.vface[n]);
-    if (vf >= 0) r += rh(Nq + vf, (Nq + vf) >> 2);
-    const real rr = -r * L.iwJ[j];
-    const size_t o = size_t(c) * splane + size_t(k0) * Nq + j;
-    if (a.mode == kRhs) {
-      rhs_out[o] = rr;
-    } else {
-      const int l = c * E * Nq + j;
-      const real dn = ra * L.DU[l] + rdt * rr;
-      const real un = L.U[l] + rb * dn;
-      du[o] = dn;
-      uh[o] = un;
-      L.U[l] = un;
+    const real iw = L.iwJ[j];
+    real un[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const auto rh = residual_in<real, D>(L)(c * E + e);
+      real r = rh(n, n >> 2);
+      if (vf >= 0) r += rh(Nq + vf, (Nq + vf) >> 2);
+      const real rr = -r * iw;
+      const size_t o = size_t(c) * splane + size_t(k0) * Nq + j;
+      if (a.mode == kRhs) {
+        static_cast<real *>(a.ext_rhs)[o] = rr;
+      } else {
+        const int l = c * E * Nq + j;
+        const real dn = ra * L.DU[l] + rdt * rr;
+        un[c] = L.U[l] + rb * dn;
+        static_cast<real *>(d.du)[o] = dn;
+        static_cast<real *>(d.uh)[o] = un[c];
+      }
     }
+    if (a.mode == kStage && vf >= 0) bad |= sbp_push<real, D>(L, e, vf, j, un[0], un[1], un[2], nbx_out);
   }
-  if (a.mode == kStage) {
-    __syncthreads();
-    sbp_push<real, D>(d, ne, L, nbx_out, a.flag);
-  }
+  if (bad) atomicOr(a.flag, 1);
 }
 
 // One launch per RK stage (or per projection / RHS) for every DG-SBP tile; persistent,
-// XCD-aligned chunks as in stage_kernel.
-template <typename real>
+// XCD-aligned chunks as in stage_kernel.  KIND, EC: as in stage_kernel.
+template <typename real, int KIND = 0, int EC = 0>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4)))
 sbp_stage_kernel(StageArgs a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   real *sm = reinterpret_cast<real *>(smem_raw);
-  real *tile = sm + a.ref_words_max;
+  real *tile = sm + (KIND != 0 ? (ref_words(KIND) + 3) & ~3 : a.ref_words_max);
   const int G = int(gridDim.x);
   const int chunk = (int(blockIdx.x) % kXcds) * (G / kXcds) + int(blockIdx.x) / kXcds;
   const int t0 = a.ranges ? read_const(a.ranges, chunk) : int((long long)chunk * a.ntiles / G);
@@ -1342,19 +1345,22 @@ sbp_stage_kernel(StageArgs a) {
   for (int t = t0; t < t1; ++t) {
     const Tile tl = read_const(a.tiles, t);
     const InstDesc &d = read_const(a.desc, tl.inst);
-    if (d.N != loaded) {
-      __syncthreads();
-      const real *ref = static_cast<const real *>(d.ref);
-      const int words = ref_words(d.N);
-      for (int i = threadIdx.x; i < words; i += blockDim.x) sm[i] = ref[i];
-      loaded = d.N;
+    if (KIND != 0 ? loaded == 0 : d.N != loaded) {
+      // the reference block, copied with the tile's data (which sbp_tile waits for)
+      constexpr int words = KIND != 0 ? (ref_words(KIND) + 3) & ~3 : 0;
+      copy_block<Threads<kBlock>, words * int(sizeof(real))>(sm, d.ref, ((ref_words(d.N) + 3) & ~3) * int(sizeof(real)));
+      loaded = KIND != 0 ? KIND : d.N;
     }
-    switch (d.N) {
+    if constexpr (KIND != 0) {
+      sbp_tile<real, KIND, EC>(a, d, tl.index, tl.k0, tl.ne, sm, tile);
+    } else {
+      switch (d.N) {
 #define ESDG_SBP_CASE(N) \
-  case make_key(N, 2): sbp_tile<real, make_key(N, 2)>(a, d, tl.index, tl.k0, tl.ne, sm, tile); break;
-      ESDG_SBP_CASE(1) ESDG_SBP_CASE(2) ESDG_SBP_CASE(3) ESDG_SBP_CASE(4)
+  case make_key(N, 2): sbp_tile<real, make_key(N, 2), 0>(a, d, tl.index, tl.k0, tl.ne, sm, tile); break;
+        ESDG_SBP_CASE(1) ESDG_SBP_CASE(2) ESDG_SBP_CASE(3) ESDG_SBP_CASE(4)
 #undef ESDG_SBP_CASE
-      default: break;
+        default: break;
+      }
     }
     __syncthreads();
   }
@@ -1429,9 +1435,24 @@ static const void *stage_fn(bool fp64, int cm, bool wadg, bool multi, bool v1, i
   return wadg ? stage_fn_unit_float_1(cm, multi, v1, kind, tile) : stage_fn_unit_float_0(cm, multi, v1, kind, tile);
 }
 
-static const void *sbp_fn(bool fp64) {
-  return fp64 ? reinterpret_cast<const void *>(&sbp_stage_kernel<double>)
-              : reinterpret_cast<const void *>(&sbp_stage_kernel<float>);
+template <typename real, int K>
+static const void *sbp_kind_fn(int tile) {
+  constexpr int EC = fixed_tile<real>(K);
+  return tile == EC ? reinterpret_cast<const void *>(&sbp_stage_kernel<real, K, EC>)
+                    : reinterpret_cast<const void *>(&sbp_stage_kernel<real, K>);
+}
+template <typename real>
+static const void *sbp_fn(int kind, int tile) {
+  switch (kind) {
+    case make_key(1, 2): return sbp_kind_fn<real, make_key(1, 2)>(tile);
+    case make_key(2, 2): return sbp_kind_fn<real, make_key(2, 2)>(tile);
+    case make_key(3, 2): return sbp_kind_fn<real, make_key(3, 2)>(tile);
+    case make_key(4, 2): return sbp_kind_fn<real, make_key(4, 2)>(tile);
+    default: return reinterpret_cast<const void *>(&sbp_stage_kernel<real>);
+  }
+}
+static const void *sbp_fn(bool fp64, int kind, int tile) {
+  return fp64 ? sbp_fn<double>(kind, tile) : sbp_fn<float>(kind, tile);
 }
 
 // Workgroups of the per-stage or multi-stage kernel (the DG-SBP kernel with sbp) that stay
@@ -1452,7 +1473,7 @@ hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int
   int lds_cu = 0;
   e = hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev);
   if (e != hipSuccess) return e;
-  const void *fn = sbp ? sbp_fn(fp64) : stage_fn(fp64, cm, wadg, multi, v1, kind, tile);
+  const void *fn = sbp ? sbp_fn(fp64, kind, tile) : stage_fn(fp64, cm, wadg, multi, v1, kind, tile);
   int n = 0;
   e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, block, lds_bytes);
   if (e != hipSuccess) return e;
@@ -1468,7 +1489,7 @@ hipError_t stage_max_blocks(bool fp64, int cm, bool wadg, bool sbp, bool v1, int
 
 hipError_t set_stage_lds_limit(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile,
                                size_t lds_bytes) {
-  if (sbp) return hipFuncSetAttribute(sbp_fn(fp64), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
+  if (sbp) return hipFuncSetAttribute(sbp_fn(fp64, kind, tile), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
   hipError_t e = hipFuncSetAttribute(stage_fn(fp64, cm, wadg, false, v1, kind, tile),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds_bytes));
   if (e != hipSuccess) return e;
@@ -1490,7 +1511,8 @@ hipError_t launch_stage(bool fp64, bool sbp, const StageArgs &a, int max_blocks,
   const int grid = stage_grid(a.ntiles, max_blocks);
   StageArgs arg = a;
   void *params[] = {&arg};
-  return hipLaunchKernel(sbp ? sbp_fn(fp64) : stage_fn(fp64, a.contraction, a.wadg != 0, false, a.v1 != 0, a.kind, a.tile),
+  return hipLaunchKernel(sbp ? sbp_fn(fp64, a.kind, a.tile)
+                             : stage_fn(fp64, a.contraction, a.wadg != 0, false, a.v1 != 0, a.kind, a.tile),
                          dim3(grid),
                          dim3(sbp ? kBlock : block), params, lds_bytes, stream);
 }

@@ -91,8 +91,11 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Default elements per workgroup of an element kind: as many as keep E*Nh <= 2 per thread
 // and the tile's LDS <= 40 KiB per 256 threads (with the reference block, several
-// workgroups stay resident per CU).
+// workgroups stay resident per CU).  DG-SBP at N = 2 in float: 13, whose 494 residual tasks are
+// two full rounds of a workgroup; 16 leaves a third round a third full, and K = 32768 takes
+// 26.4 us a stage against 20.2.
 int default_epb(int D, size_t word, bool wadg, int P, int block) {
+  if (D == make_key(2, 2) && word == 4) return 13;
   int best = 1;
   for (int E = 1; E <= 64; E *= 2) {
     if (E * dim_Nh(D) > 2 * block) break;
@@ -154,7 +157,7 @@ struct esdg_swe {
   size_t lds_bytes = 0;            // dynamic LDS of a workgroup
   size_t limit_bytes = 0;          // the tile limit's count of it (limit_words in device_types.hpp)
   int block = kBlock;              // stage-kernel workgroup size (kBlockWide if every kind is wide)
-  int kind = 0;                    // the one element kind of every instance (modal), else 0
+  int kind = 0;                    // the one element kind of every instance, else 0
   int tile = 0;                    // its elements per tile
   bool cooperative = true;         // multi-stage launches through hipLaunchCooperativeKernel (false
                                    // once the residency probe at bind saw the whole grid resident)
@@ -492,8 +495,8 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
       return ESDG_EINVAL;
     }
   }
-  // one modal kind for every instance: the stage kernel built for that kind alone
-  if (s->refs.size() == 1 && !s->sbp) s->kind = s->refs.begin()->first;
+  // one kind for every instance: the stage kernel built for that kind alone
+  if (s->refs.size() == 1) s->kind = s->refs.begin()->first;
   // workgroup size: kBlockWide when every kind is wide (its reference block is then shared
   // by twice the elements), else kBlock
   {
