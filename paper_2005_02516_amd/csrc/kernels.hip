@@ -32,6 +32,7 @@
 #include <algorithm>
 
 #include <cmath>
+#include <map>
 #include <type_traits>
 
 #include "device_types.hpp"
@@ -260,7 +261,9 @@ template <> struct RowsPerThread<float, 1> { static constexpr int value = 2; };
 template <> struct RowsPerThread<float, 3> { static constexpr int value = 2; };
 template <> struct RowsPerThread<float, make_key(1, 2)> { static constexpr int value = 2; };   // DG-SBP: 6 + 6 nodes
 template <> struct RowsPerThread<float, make_key(3, 2)> { static constexpr int value = 2; };   // 18 + 12
-// The tile size the single-kind kernel of a kind is built for (0: none).
+// The tile size a kind's kernel is built for (0: none), so that every LDS offset is an
+// immediate: the fastest for large meshes (FP32 N = 2, K = 65522: 43.7 us a stage at 14, 50.6
+// at 12; with run-time offsets 49 and 55).
 template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) {
   const bool f = sizeof(real) == 4;
   switch (kind) {
@@ -275,6 +278,18 @@ template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) 
     default: return 0;
   }
 }
+
+// A second one: what small meshes (one tile for each of 1024 workgroups) or launches of
+// several degrees, whose largest tile sets the LDS of all, take instead.
+template <typename real> __host__ __device__ constexpr int other_tile(int kind) {
+  const bool f = sizeof(real) == 4;
+  return kind == 1 ? (f ? 16 : 12) : kind == 2 ? (f ? 12 : 8) : 0;
+}
+// Per stage without and with: FP32 N = 1, K = 8192 4.87 -> 4.35 us, FP64 N = 2, K = 8192 8.47 ->
+// 7.92, K = 1800 6.08 -> 5.53.
+// EC of the kernel for several kinds whose tiles have those sizes (an ensemble of 45944
+// elements, N = 2..4, FP32: 72.8 us a stage with run-time offsets, 66.2 with these).
+constexpr int kFixedTiles = -1;
 
 // What changes from stage to stage of a launch.
 struct StageRun {
@@ -1003,9 +1018,10 @@ __device__ __forceinline__ void residency_probe(const StageArgs &a) {
   }
 }
 
-// Threads of a kernel built for one kind (as the host launches it; 0: not a constant).
-__host__ __device__ constexpr int stage_kernel_threads(int kind) {
-  return kind == 0 ? 0 : wide_kind(kind) ? kBlockWide : kBlock;
+// Threads of a kernel built for one kind, or for several with fixed tiles (as the host launches
+// it; 0: not a constant).
+__host__ __device__ constexpr int stage_kernel_threads(int kind, int tile) {
+  return kind == 0 ? (tile == kFixedTiles ? kBlock : 0) : wide_kind(kind) ? kBlockWide : kBlock;
 }
 
 template <typename real, int CM, bool WADG, bool MULTI, bool V1, int KIND = 0, int EC = 0>
@@ -1015,7 +1031,7 @@ stage_kernel(StageArgs a) {
     residency_probe(a);
     return;
   }
-  constexpr int NT = stage_kernel_threads(KIND);
+  constexpr int NT = stage_kernel_threads(KIND, EC);
   extern __shared__ __align__(16) unsigned char smem_raw[];
   real *sm = reinterpret_cast<real *>(smem_raw);
   real *tile = sm + (KIND != 0 ? (ref_words(KIND) + 3) & ~3 : a.ref_words_max);
@@ -1054,11 +1070,22 @@ stage_kernel(StageArgs a) {
         copy_block<Threads<NT>, words * int(sizeof(real))>(sm, d.ref, ((ref_words(d.N) + 3) & ~3) * int(sizeof(real)));
         loaded_N = KIND != 0 ? KIND : d.N;
       }
+#define ESDG_STAGE_TILE(D, E)                                                                                  \
+  if (MULTI && resident) resident_tile<real, D, CM, WADG, E, NT>(a, d, t, tl.index, tl.k0, tl.ne, sm, tile);   \
+  else stage_tile<real, D, CM, WADG, MULTI, E, NT>(a, r, d, tl.index, tl.k0, tl.ne, sm, tile)
 #define ESDG_STAGE_CASE(D)                                                                                     \
-  case D:                                                                                                      \
-    if (MULTI && resident) resident_tile<real, D, CM, WADG, EC, NT>(a, d, t, tl.index, tl.k0, tl.ne, sm, tile); \
-    else stage_tile<real, D, CM, WADG, MULTI, EC, NT>(a, r, d, tl.index, tl.k0, tl.ne, sm, tile);               \
-    break;
+  case D: {                                                                                                    \
+    constexpr int E1 = EC == kFixedTiles ? fixed_tile<real>(D) : EC;                                           \
+    constexpr int E2 = EC == kFixedTiles ? other_tile<real>(D) : 0;                                            \
+    if constexpr (E2 == 0) {                                                                                   \
+      ESDG_STAGE_TILE(D, E1);                                                                                  \
+    } else {                                                                                                   \
+      if (d.E == E1) { ESDG_STAGE_TILE(D, E1); }                                                               \
+      else if (d.E == E2) { ESDG_STAGE_TILE(D, E2); }                                                          \
+      else { ESDG_STAGE_TILE(D, 0); }                                                                          \
+    }                                                                                                          \
+    break;                                                                                                     \
+  }
       if constexpr (KIND != 0) {     // every tile is of this kind (the host's choice of kernel)
         switch (KIND) {
           ESDG_STAGE_CASE(KIND)
@@ -1076,6 +1103,7 @@ stage_kernel(StageArgs a) {
           default: break;
         }
       }
+#undef ESDG_STAGE_TILE
 #undef ESDG_STAGE_CASE
       if (multi && !resident) publish(a, t, a.stage0 + s + 1);
       else __syncthreads();
@@ -1381,7 +1409,7 @@ const void *stage_fn_unit_double_1(int cm, bool multi, bool v1, int kind, int ti
 
 #if defined(ESDG_UNIT_REAL)
 template <bool V1>
-static const void *unit_fn(int cm, bool multi) {
+static const void *unit_fn(int cm, bool multi, int tile) {
   using real = ESDG_UNIT_REAL;
   constexpr bool W = ESDG_UNIT_WADG != 0;
   if constexpr (std::is_same<real, float>::value) {
@@ -1389,19 +1417,27 @@ static const void *unit_fn(int cm, bool multi) {
       return multi ? reinterpret_cast<const void *>(&stage_kernel<float, kMfmaBf16x3, W, true, V1>)
                    : reinterpret_cast<const void *>(&stage_kernel<float, kMfmaBf16x3, W, false, V1>);
   }
+  if constexpr (!V1)
+    if (tile == kFixedTiles)
+      return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, false, 0, kFixedTiles>)
+                   : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, false, 0, kFixedTiles>);
   return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, V1>)
                : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, V1>);
+}
+template <int K, int EC>
+static const void *tile_fn(bool multi) {
+  using real = ESDG_UNIT_REAL;
+  constexpr bool W = ESDG_UNIT_WADG != 0;
+  return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, false, K, EC>)
+               : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, false, K, EC>);
 }
 template <int K>
 static const void *kind_fn(bool multi, int tile) {
   using real = ESDG_UNIT_REAL;
-  constexpr bool W = ESDG_UNIT_WADG != 0;
-  constexpr int EC = fixed_tile<real>(K);
-  if (tile == EC)
-    return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, false, K, EC>)
-                 : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, false, K, EC>);
-  return multi ? reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, true, false, K>)
-               : reinterpret_cast<const void *>(&stage_kernel<real, kMfmaNative, W, false, false, K>);
+  if (tile == fixed_tile<real>(K)) return tile_fn<K, fixed_tile<real>(K)>(multi);
+  if constexpr (other_tile<real>(K) != 0)
+    if (tile == other_tile<real>(K)) return tile_fn<K, other_tile<real>(K)>(multi);
+  return tile_fn<K, 0>(multi);
 }
 const void *ESDG_UNIT_FN(ESDG_UNIT_REAL, ESDG_UNIT_WADG)(int cm, bool multi, bool v1, int kind, int tile) {
   if (cm != kMfmaBf16x3 && !v1) {  // one variant-0 kind: that kind's own build
@@ -1414,7 +1450,7 @@ const void *ESDG_UNIT_FN(ESDG_UNIT_REAL, ESDG_UNIT_WADG)(int cm, bool multi, boo
       default: break;
     }
   }
-  return v1 ? unit_fn<true>(cm, multi) : unit_fn<false>(cm, multi);
+  return v1 ? unit_fn<true>(cm, multi, tile) : unit_fn<false>(cm, multi, tile);
 }
 #endif
 
@@ -1451,6 +1487,18 @@ static const void *sbp_fn(int kind, int tile) {
     default: return reinterpret_cast<const void *>(&sbp_stage_kernel<real>);
   }
 }
+// StageArgs.tile of a launch of several kinds with E elements to a tile of kind D (epb): the
+// kernel with fixed tiles holds one size for each of N = 3, 4 and 5 (of which nothing fits
+// better, see fixed_tile) and any for N = 1 and 2.
+int mixed_tile(bool fp64, const std::map<int, int> &epb);
+int mixed_tile(bool fp64, const std::map<int, int> &epb) {
+  for (const auto &kv : epb) {
+    if (key_variant(kv.first) != 0) return 0;
+    if (kv.first > 2 && kv.second != (fp64 ? fixed_tile<double>(kv.first) : fixed_tile<float>(kv.first))) return 0;
+  }
+  return kFixedTiles;
+}
+
 static const void *sbp_fn(bool fp64, int kind, int tile) {
   return fp64 ? sbp_fn<double>(kind, tile) : sbp_fn<float>(kind, tile);
 }

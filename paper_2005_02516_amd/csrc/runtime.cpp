@@ -19,6 +19,7 @@
 #include "host_setup.hpp"
 
 namespace esdg {
+int mixed_tile(bool fp64, const std::map<int, int> &epb);
 hipError_t set_stage_lds_limit(bool fp64, int cm, bool wadg, bool sbp, bool v1, int kind, int tile,
                                size_t lds_bytes);
 hipError_t launch_stage(bool fp64, bool sbp, const StageArgs &a, int max_blocks, size_t lds_bytes, int block,
@@ -524,6 +525,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     tile = std::max(tile, size_t(tile_words(D, E, s->wadg)));
     limit = std::max(limit, size_t(limit_words(D, E, s->wadg, P)));
   }
+  if (s->kind == 0) s->tile = mixed_tile(s->fp64, s->epb);
   if (s->shapes && (s->contraction != 0 || s->v1)) {
     g_init_error = "esdg_swe_init: tile shapes other than the default need matrix_cores 0 or 1, FP64 or FP32 "
                    "and the (N+1)-point quadrature";
