@@ -66,10 +66,10 @@ __host__ __device__ constexpr long long elem_work(int D) {
 // Relative cost of one element of kind D in a stage, for splitting the tiles of a
 // mixed-degree launch into ranges of equal cost.  The operation count overstates the higher
 // degrees (their phases keep more lanes busy), so the default-quadrature modal kinds take
-// measured per-element stage times instead: single-degree meshes of 131072 elements, FP32,
-// tuned tiles of 256-thread workgroups, relative to N=2 (0.87 ns) in hundredths; the other
+// measured per-element stage times instead: single-degree meshes of 65522 elements, FP32,
+// tuned tiles, relative to N=2 (0.67 ns) in hundredths; the other
 // kinds scale their degree's figure by their operation count relative to it.
-constexpr long long kStageCost[6] = {0, 46, 100, 182, 384, 724};
+constexpr long long kStageCost[6] = {0, 53, 100, 166, 322, 526};
 __host__ __device__ constexpr long long elem_cost(int D) {
   return kStageCost[key_N(D)] * elem_work(D) / elem_work(key_N(D));
 }
