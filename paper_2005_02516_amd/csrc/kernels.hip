@@ -280,13 +280,13 @@ template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) 
 }
 
 // A second one: what small meshes (one tile for each of 1024 workgroups) or launches of
-// several degrees, whose largest tile sets the LDS of all, take instead.
+// several degrees, whose largest tile sets the LDS of all, take instead.  Per stage without and
+// with: FP32 N = 1, K = 8192 4.87 -> 4.35 us, FP64 N = 2, K = 8192 8.47 -> 7.92, K = 1800 6.08 ->
+// 5.53.
 template <typename real> __host__ __device__ constexpr int other_tile(int kind) {
   const bool f = sizeof(real) == 4;
   return kind == 1 ? (f ? 16 : 12) : kind == 2 ? (f ? 12 : 8) : 0;
 }
-// Per stage without and with: FP32 N = 1, K = 8192 4.87 -> 4.35 us, FP64 N = 2, K = 8192 8.47 ->
-// 7.92, K = 1800 6.08 -> 5.53.
 // EC of the kernel for several kinds whose tiles have those sizes (an ensemble of 45944
 // elements, N = 2..4, FP32: 72.8 us a stage with run-time offsets, 66.2 with these).
 constexpr int kFixedTiles = -1;
@@ -694,14 +694,19 @@ __device__ __forceinline__ void residual_tile(int ne, LT &L) {
       e = int(rest / rows);
       b = int(rest) - __umul24(unsigned(e), rows);
     };
-    const int nv = 2 * ne * VB, ntask = nv + 2 * ne * FB;
-    for (int t = tid; t < ntask; t += nth) {
+    // the face tasks start on a wave of their own where that adds no round: a wave with tasks of
+    // both sorts runs both loops (DG-SBP N = 4, K = 32768 49.6 -> 47.3 us a stage, FP64 N = 4,
+    // K = 20402 98.3 -> 95)
+    const int nv = 2 * ne * VB, nf = 2 * ne * FB, whole = (nv + 63) & ~63;
+    const int nv1 = (whole + nf + nth - 1) / nth > (nv + nf + nth - 1) / nth ? nv : whole;
+    for (int t = tid; t < nv1 + nf; t += nth) {
       int p, e, b;
-      if (t < nv) {
+      if (t < nv1) {
         split(t, VB, p, e, b);
-        row_sums<real, N, R, Nh / 2, 2 * Nq>(e, b * R, p, p * (Nh / 2), Nh % 2 != 0 && p != 0, L.ST + 2 * b * R, L);
+        if (t < nv)
+          row_sums<real, N, R, Nh / 2, 2 * Nq>(e, b * R, p, p * (Nh / 2), Nh % 2 != 0 && p != 0, L.ST + 2 * b * R, L);
       } else {
-        split(t - nv, FB, p, e, b);
+        split(t - nv1, FB, p, e, b);
         row_sums<real, N, R, Nq / 2, 2 * Nfq>(e, Nq + b * R, p, p * (Nq / 2), Nq % 2 != 0 && p != 0, L.FT + 2 * b * R, L);
       }
     }
@@ -764,13 +769,13 @@ __device__ __forceinline__ bool wait_neighbours(const StageArgs &a, int t, int t
   return __syncthreads_and(ok) != 0;
 }
 
-// The same wait for a resident tile, whose caller puts the barrier: false, with flag bit 1 set,
-// once a wait has given up (`waits` false: do not wait).  Wave 0 only.
+// The same wait for a resident tile, by every wave that calls it and for that wave alone: false,
+// with flag bit 1 set, once a wait has given up (`waits` false: do not wait).
 __device__ __forceinline__ bool poll_neighbours(const StageArgs &a, int t, int target, bool waits) {
   bool ok = waits;
-  if (waits && threadIdx.x < 64) {
+  if (waits) {
     const int b = read_const(a.nbr_off, t), e = read_const(a.nbr_off, t + 1);
-    for (int j = b + int(threadIdx.x); j < e; j += 64) {
+    for (int j = b + (int(threadIdx.x) & 63); j < e; j += 64) {
       const int u = read_const(a.nbr_idx, j);
       int spins = 0;
       while (__hip_atomic_load(a.progress + u * kProgressStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
@@ -820,6 +825,16 @@ __device__ __forceinline__ auto fetched_neighbours(const LT &L) {
   };
 }
 
+// First of the interface tasks of this thread: in the modal kinds from the last wave on, since
+// the pair loop gives its longer tasks (volume rows) to the first waves (FP32 N = 3, K = 20402
+// 29.5 -> 28.8 us a stage, N = 1, K = 65522 23.4 -> 22.9).  The wide kinds' last waves have the
+// longer ones, and in DG-SBP at N = 3 the third wave has both sorts (K = 32768 34.3 us; 35.8
+// from the last wave on).
+template <int N, class LT>
+__device__ __forceinline__ int interface_tid() {
+  return wide_kind(N) || key_sbp(N) ? phase_tid() : phase_tid() ^ (threads<LT>() - 64);
+}
+
 // Phase 3: interface terms of the face rows (Section 2.8): W_f [ nJ . f_S(u~, u~+) + 1/2 g h
 // (H+ - Href) nJ ] - LF penalty, one task per (element, face node), into the first three words
 // of the node's four in the neighbour block (the lift adds them).  A pass of its own so that a
@@ -828,7 +843,7 @@ __device__ __forceinline__ auto fetched_neighbours(const LT &L) {
 template <typename real, int N, class LT, class FN>
 __device__ __forceinline__ void interface_tile(const InstDesc &d, int ne, LT &L, FN neighbour) {
   constexpr int Nq = dim_Nq(N), Nfq = dim_Nfq(N);
-  for (int i = phase_tid(); i < ne * Nfq; i += threads<LT>()) {
+  for (int i = interface_tid<N, LT>(); i < ne * Nfq; i += threads<LT>()) {
     const int e = int(unsigned(i) / unsigned(Nfq)), f = i - __umul24(unsigned(e), unsigned(Nfq));
     real t0, t1, t2;
     real nbp[4];
@@ -936,7 +951,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs &a, const StageRun &r
 // before (one stage body for all launches, counts packed 32 to a line) and now: FP32 N = 3,
 // K = 8192 8.66 -> 7.33 us, N = 2 K = 8192 7.3 -> 6.3, N = 1 K = 8192 6.05 -> 4.91, FP64
 // N = 2 K = 8192 10.05 -> 8.65; with packed counts this loop alone made N = 1 7.1 us (each
-// publish took its line from all the pollers of 32 tiles).
+// publish took its line from all the pollers of 32 tiles).  With the wait and the interface
+// terms on the waves that have them, and no barrier before: N = 3, K = 512 5.56 -> 5.07, K = 8192
+// 7.26 -> 7.1, N = 1, K = 8192 4.35 -> 4.07, FP64 N = 2 7.9 -> 7.45, N = 3, K = 3200 7.3 -> 6.8.
 template <typename real, int N, int CM, bool WADG, int EC, int NT>
 __device__ __forceinline__ void resident_tile(const StageArgs &a, const InstDesc &d, int t, int index, int k0, int ne,
                                               real *sm, real *tile) {
@@ -959,20 +976,22 @@ __device__ __forceinline__ void resident_tile(const StageArgs &a, const InstDesc
     r.rk_b = a.rk_b5[s5];
     residual_tile<real, N, RowsPerThread<real, N>::value>(ne, L);
     if (s > 0) {
-      waits = poll_neighbours(a, t, a.stage0 + s, waits);
-      __syncthreads();
-      // from here to its publish the tile is on its neighbours' critical path (their next
-      // stage waits for its pushes), while the other workgroups on the CU that are still in
-      // their pair loop have slack: raise this workgroup's wave priority until the publish
-      __builtin_amdgcn_s_setprio(2);
-      const real *nbx = static_cast<const real *>(d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4;
-      interface_tile<real, N>(d, ne, L, [nbx](int i, real *v) {
-        load_coherent(nbx + 4 * size_t(unsigned(i)), v);
-      });
+      // a wave with interface tasks waits and runs them while others are in their pair loop
+      if (__builtin_amdgcn_readfirstlane(interface_tid<N, LT>()) < ne * Nfq) {
+        waits = poll_neighbours(a, t, a.stage0 + s, waits);
+        const real *nbx = static_cast<const real *>(d.nbx[r.in_buf]) + size_t(k0) * Nfq * 4;
+        interface_tile<real, N>(d, ne, L, [nbx](int i, real *v) {
+          load_coherent(nbx + 4 * size_t(unsigned(i)), v);
+        });
+      }
     } else {
       interface_tile<real, N>(d, ne, L, fetched_neighbours<real>(L));
     }
     __syncthreads();
+    // from here to its publish the tile is on its neighbours' critical path (their next
+    // stage waits for its pushes), while the other workgroups on the CU that are still in
+    // their pair loop have slack: raise this workgroup's wave priority until the publish
+    __builtin_amdgcn_s_setprio(2);
     lift_update<real, N, CM, WADG>(a, r, d, kStage, k0, ne, L, last);
     __syncthreads();
     project_tile<real, N, CM, WADG>(d, k0, ne, L, static_cast<real *>(d.ut[r.out_buf]), static_cast<real *>(d.nbx[r.out_buf]),
