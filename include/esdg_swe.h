@@ -159,9 +159,9 @@ typedef struct {
   int32_t use_graph;        /* nonzero: esdg_swe_step replays HIP graphs of its RK stages    */
   int32_t elems_per_block[6]; /* elements per workgroup for degree N = index (1..5); 0 = the
                                  library's default for that degree; index 0 unused            */
-  int32_t matrix_cores;     /* projection/lift contractions with constant operators: 0 or 1 =
-                               vector ALUs, 2 = matrix cores (MFMA) in the bulk precision;
-                               ESDG_FP32_BF16X3 always uses the split-bf16 matrix-core path  */
+  int32_t matrix_cores;     /* 0, 1 or 2, without effect: the projection/lift contractions with
+                               constant operators run on the matrix cores (MFMA) in the bulk
+                               precision, with ESDG_FP32_BF16X3 as split-bf16 products       */
   int32_t fused_steps;      /* how esdg_swe_step launches its RK stages: 0 = one launch per
                                stage (HIP graphs if use_graph); 1 = all stages of the call in
                                one launch whose workgroups are all resident (an ordinary
@@ -177,12 +177,13 @@ typedef struct {
   int32_t mass_inverse;     /* ESDG_MASS_STORED | ESDG_MASS_WEIGHT_ADJUSTED (modal scheme)     */
   int32_t tile_shape[6];    /* residual-phase tile shape per degree N = index (1..5), packed
                                (R << 4) | P: R rows per thread (1, or 2 in FP32 where 2 divides
-                               Nq and Nfq), P column parts (1..4) whose partial sums the lift
-                               adds; 0 = the library's default ((2 << 4) | 2 in FP32 at N = 1
-                               and 3, else (1 << 4) | 2); another shape returns ESDG_EINVAL.
-                               A shape other than the default needs matrix_cores 0 or 1 and
-                               the (N+1)-point quadrature.  The shape changes the summation
-                               order only.                                                   */
+                               Nq and Nfq), P column parts (1..4); 0 = the library's default
+                               ((2 << 4) | 2 in FP32 at N = 1 and 3, (1 << 4) | 1 at N = 5,
+                               else (1 << 4) | 2); another shape returns ESDG_EINVAL.  A shape
+                               other than the default needs matrix_cores 0 or 1 and the
+                               (N+1)-point quadrature.  P enters the limit of elems_per_block;
+                               the residual has one split for each degree, so the shape has
+                               no other effect.                                              */
   int32_t scheme;           /* ESDG_SCHEME_MODAL | ESDG_SCHEME_SBP (every instance a caller's
                                DG-SBP rule; precision FP64 or FP32, flux EC or LF, walls
                                allowed; contractions, mass_inverse and fused_steps do not apply) */

@@ -2,10 +2,9 @@
 residual phase's tile shape (R rows per thread, P column parts).
 
 The stage kernel's LDS footprint, and so its occupancy, grows with the number of elements
-per workgroup E, while small E leaves threads idle in every phase; the residual phase
-deals (element, R rows, column part) tasks to the 256 threads, so R and P set how evenly
-its rounds fill and how often a column's node record is reused; P also sizes the partial
-sums in LDS.  The best choice depends on the degree N, the precision and how many
+per workgroup E, while small E leaves threads idle in every phase.  The tile shape enters
+the library's limit on E (P) and nothing else: the kernels have one split of the residual
+for each degree.  The best choice depends on the degree N, the precision and how many
 elements there are in total.  ``tune`` times a few LSRK steps for every candidate E with
 the default shape, then every shape the kernel is compiled for at the best few E (HIP
 events on the solver's stream), and records the fastest (E, R, P) in a JSON cache keyed by

@@ -10,7 +10,7 @@
 //      nonzero block of Q_skew = Q_h - Q_h^T (volume-volume and volume-surface; the zero
 //      surface-surface block is skipped), with the element's physical operator built on
 //      the fly from averaged geometric factors (Section 2.7) and the EC flux of
-//      Section 2.8; each thread owns R rows of one element so a column's node record is
+//      Section 2.8; each task takes R rows of one element so a column's node record is
 //      read once for R rows.  The bathymetry source is folded in as
 //      1/2 g h_m (H_n - Href) Q_mn (exact because Q_h 1 = 0);
 //   3. interface flux f_S(u~+, u~), boundary half of the source and optional local
@@ -25,12 +25,15 @@
 // boundary (one launch per stage) or, in a multi-stage launch, per-tile progress counts
 // that a tile waits on before it reads its neighbours' values.
 //
+// The products with the constant operators (lift, projection) run on the matrix cores, with the
+// columns (field, element) of the tile side by side; the pair loop is a Hadamard product and
+// stays on the vector ALUs.  What bounds a stage is the chain of these short phases.
+//
 // Depth is carried as the free-surface anomaly eta = h + b - Href (Href a per-instance
 // constant), so the projection works on v1 - g Href and no quantity of size g H is
 // rounded to the bulk precision; the conversions to h are done in double.
 #include <hip/hip_runtime.h>
 #include <algorithm>
-
 #include <cmath>
 #include <map>
 #include <type_traits>
@@ -209,7 +212,7 @@ __device__ __forceinline__ auto cols_out(real *x) {
   return [x](int i, int c, real v) { x[__umul24(unsigned(c), unsigned(M)) + i] = v; };
 }
 
-// LDS carve-up of one tile (see lds_words()).
+// LDS carve-up of one tile (see tile_words()).
 template <typename real, int N, int EC, int NTH>
 struct Lds {
   static constexpr int NT = NTH;
@@ -262,8 +265,8 @@ template <> struct RowsPerThread<float, 3> { static constexpr int value = 2; };
 template <> struct RowsPerThread<float, make_key(1, 2)> { static constexpr int value = 2; };   // DG-SBP: 6 + 6 nodes
 template <> struct RowsPerThread<float, make_key(3, 2)> { static constexpr int value = 2; };   // 18 + 12
 // The tile size a kind's kernel is built for (0: none), so that every LDS offset is an
-// immediate: the fastest for large meshes (FP32 N = 2, K = 65522: 43.7 us a stage at 14, 50.6
-// at 12; with run-time offsets 49 and 55).
+// immediate: the size that is fastest for large meshes (FP32 N = 2, K = 65522: 43.7 us a stage
+// at 14 so, 50.6 at 12 with run-time offsets).
 template <typename real> __host__ __device__ constexpr int fixed_tile(int kind) {
   const bool f = sizeof(real) == 4;
   switch (kind) {
@@ -1479,11 +1482,7 @@ const void *ESDG_UNIT_FN(ESDG_UNIT_REAL, ESDG_UNIT_WADG)(int cm, bool multi, boo
 // The stage kernel for a precision, contraction mode, mass inverse and launch kind (one
 // launch per stage, or all stages of a step call in one multi-stage launch).  One launch
 // per stage runs the per-stage instantiation, built without the waits, resident tiles and
-// coherent pushes: its scalar registers spill far less (FP32 all kinds 36 against 102),
-// and each reload of a spilled one is a vector instruction.  (FP32 once ran its
-// multi-stage instantiation for single stages as well, measured faster then; with the
-// single-kind builds and the current task layout the per-stage one is faster on one box:
-// N=1..5 by 11, 7.5, 6.5, 2 and 2.3 %, the mixed-degree ensemble by 5 %.)
+// coherent pushes.
 static const void *stage_fn(bool fp64, int cm, bool wadg, bool multi, bool v1, int kind, int tile) {
   if (fp64)
     return wadg ? stage_fn_unit_double_1(cm, multi, v1, kind, tile) : stage_fn_unit_double_0(cm, multi, v1, kind, tile);

@@ -106,7 +106,7 @@ int default_epb(int D, size_t word, bool wadg, int P, int block) {
   return best;
 }
 
-// Default tile shape of the residual phase (kernels.hip: RowsPerThread, DefaultParts): two
+// Default of the tile shape option, as it has been (its P enters limit_words): two
 // rows per thread in float at N = 1 and 3 of the default quadrature, else one; one column
 // chunk at N = 5 of the default quadrature, else two.  (DG-SBP tiles use one row and two
 // chunks always.)
