@@ -11,6 +11,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -696,12 +697,17 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     const InstanceHost &H = s->host[i];
     const Offsets &f = s->off[i];
     if (!s->sbp) {
-      // metric factors as quads [K][Nh][4]
+      // metric factors as quads [K][Nh][4], in one pass over the four planes
       const size_t nodes = size_t(H.K) * dim_Nh(H.key);
-      std::vector<double> g(nodes * 4);
-      for (size_t c = 0; c < 4; ++c)
-        for (size_t j = 0; j < nodes; ++j) g[4 * j + c] = H.geo[c * nodes + j];
-      keep.push_back(to_bulk(g, s->fp64));
+      const double *g = H.geo.data();
+      keep.push_back(std::vector<unsigned char>(nodes * 4 * s->word));
+      auto quads = [&](auto *out) {
+        using real = std::remove_pointer_t<decltype(out)>;
+        for (size_t j = 0; j < nodes; ++j, out += 4)
+          for (size_t c = 0; c < 4; ++c) out[c] = real(g[c * nodes + j]);
+      };
+      if (s->fp64) quads(reinterpret_cast<double *>(keep.back().data()));
+      else quads(reinterpret_cast<float *>(keep.back().data()));
       if ((st = upload(s, f.geo, keep.back().data(), keep.back().size()))) return st;
     }
     // w J and the bathymetry at the hybrid nodes, in double (diagnostics, rest depth)
@@ -736,7 +742,14 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
         size_t o = size_t(s->tiles[t].index) * ST;
         // an array [E][m] of the block from x [K][m]
         auto put_rows = [&](const double *x, size_t m, auto value) {
-          for (size_t j = 0; j < ne * m; ++j) put(o + j, value(x[k0 * m + j]));
+          const double *from = x + k0 * m;
+          if (s->fp64) {
+            double *to = reinterpret_cast<double *>(blk.data()) + o;
+            for (size_t j = 0; j < ne * m; ++j) to[j] = value(from[j]);
+          } else {
+            float *to = reinterpret_cast<float *>(blk.data()) + o;
+            for (size_t j = 0; j < ne * m; ++j) to[j] = float(value(from[j]));
+          }
           o += E * m;
         };
         auto same = [](double v) { return v; };
