@@ -121,10 +121,16 @@ __device__ inline float bf16_value(unsigned short h) { return __uint_as_float(un
 // Row and column indices beyond the matrices are clamped (the loads stay inside them, the
 // results are dropped), and so is the last k-quad, whose B values beyond KD are zeroed, so
 // the loop has no bounds checks: a step is one LDS word of A and of B per 16x16x4 product.
+// The steps go to two accumulators in turn, added at the end: half as long a chain of roundings
+// and of dependent products.  RMS error of an FP32 right-hand side against 64 bits with one
+// accumulator and with two, relative to two partial sums on the vector ALUs (geometric means over
+// meshes, options and seeds): N = 1..5 1.008, 1.036, 1.024, 1.074, 1.033 and 0.993, 0.998, 0.964,
+// 0.979, 0.912; N+2 points 1.098 and 1.003.  Time: N = 2, K = 65522 39.7 -> 40.0 us a stage, the
+// other degrees within 0.4 %.
 template <int M, int KD, typename real, class FA, class FB, class FC>
 __device__ __forceinline__ void gemm_native(int ncol, int nwaves, FA a, int lda, FB b, FC c_store) {
   typedef typename Acc<real>::type acc_t;
-  constexpr int MB = (M + 15) / 16, KS = (KD + 3) / 4;
+  constexpr int MB = (M + 15) / 16, KS = (KD + 3) / 4, CH = KS > 1 ? 2 : 1;
   const int t = phase_tid(), lane = t & 63, lrow = lane & 15, quad = lane >> 4;
   const int nblk = MB * ((ncol + 15) >> 4);
 #pragma unroll 1
@@ -133,19 +139,19 @@ __device__ __forceinline__ void gemm_native(int ncol, int nwaves, FA a, int lda,
     const int row = bi * 16 + lrow, col = bj * 16 + lrow;
     const real *ap = a(M % 16 == 0 || row < M ? row : M - 1);
     const auto bp = b(col < ncol ? col : ncol - 1);
-    acc_t acc = {0, 0, 0, 0};
+    acc_t acc[CH] = {};
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int k = 4 * s + quad;
       const bool in = KD % 4 == 0 || s + 1 < KS || k < KD;
       const int kc = in ? k : KD - 1;
       const real av = ap[kc * lda], bv = bp(kc, s);
-      acc = mfma(av, in ? bv : real(0), acc);
+      acc[s % CH] = mfma(av, in ? bv : real(0), acc[s % CH]);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int i = bi * 16 + acc_row<real>(quad, r);
-      if (i < M && col < ncol) c_store(i, col, acc[r]);
+      if (i < M && col < ncol) c_store(i, col, CH == 1 ? acc[0][r] : acc[0][r] + acc[CH - 1][r]);
     }
   }
 }
@@ -717,7 +723,7 @@ __device__ __forceinline__ void residual_tile(int ne, LT &L) {
 }
 
 // Residual r_h of column c = (field, element) at hybrid node k: its two parts and, on the face
-// rows, the interface terms.
+// rows, the interface terms, which are added to the first part.
 template <typename real, int D, class LT>
 __device__ __forceinline__ auto residual_in(const LT &L) {
   constexpr int Nq = dim_Nq(D), Nfq = dim_Nfq(D), Nh = dim_Nh(D);
@@ -728,13 +734,13 @@ __device__ __forceinline__ auto residual_in(const LT &L) {
     const real *p0 = R + __umul24(unsigned(c), unsigned(Nh)), *p1 = p0 + 3 * E * Nh;
     const real *pf = nb + __umul24(unsigned(e), unsigned(4 * Nfq)) + f;
     return [=](int k, int s) {     // s = k / 4, which settles most of the tests at compile time
-      real v = p0[k] + p1[k];
+      real v = p0[k];
       if (4 * s + 3 >= Nq) {
         const bool face = 4 * s >= Nq || k >= Nq;
         const real x = pf[face ? 4 * (k - Nq) : 0];
         v += face ? x : real(0);
       }
-      return v;
+      return v + p1[k];
     };
   };
 }
