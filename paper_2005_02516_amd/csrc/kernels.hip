@@ -1052,8 +1052,20 @@ __host__ __device__ constexpr int stage_kernel_threads(int kind, int tile) {
   return kind == 0 ? (tile == kFixedTiles ? kBlock : 0) : wide_kind(kind) ? kBlockWide : kBlock;
 }
 
+// Waves per SIMD that a kernel's registers have to allow.  Four, what the LDS of the default tile
+// sizes leaves room for, except in the builds with run-time offsets: those also serve small tiles,
+// of which more fit a CU (five workgroups where registers and LDS meet, six in FP32 at N = 4,
+// and three of 512 threads at N = 5).  Left at four they took up to 101 registers, so that fewer
+// workgroups than tiles were resident: FP32 N = 3, K = 4608, four elements to a tile 8.5 -> 11.6 us
+// a stage, FP64 N = 2, four 9.8 -> 18.6, FP32 N = 5, two 37.6 -> 49.0.  FP64 N = 4 and 5 have no
+// room in LDS for a fifth (a third at N = 5).
+template <typename real> __host__ __device__ constexpr int stage_waves(int kind, int tile) {
+  if (kind == 0 || key_variant(kind) != 0 || tile != 0) return 4;
+  return kind <= 3 ? 5 : sizeof(real) == 4 ? 6 : 4;
+}
+
 template <typename real, int CM, bool WADG, bool MULTI, bool V1, int KIND = 0, int EC = 0>
-__global__ void __launch_bounds__(kBlockWide) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__(kBlockWide) __attribute__((amdgpu_waves_per_eu(stage_waves<real>(KIND, EC))))
 stage_kernel(StageArgs a) {
   if (MULTI && a.mode == kProbe) {
     residency_probe(a);
