@@ -281,10 +281,12 @@ esdg_status esdg_swe_reference_level(const esdg_swe *s, int32_t inst, double *Hr
  * element; Nq the volume nodes the kernels use, a caller's rule counted with its padding). */
 esdg_status esdg_swe_query(const esdg_swe *s, int32_t inst, int32_t *out6);
 
-/* Launch plan (after bind): out = {element tiles, resident workgroups of the stage kernel,
- * LDS bytes per workgroup, step mode (0 = one launch per stage, 1 = one launch per step
- * call re-reading tiles every stage, 2 = one launch per step call with tiles resident in
- * LDS)}.  ESDG_ESTATE before bind. */
+/* Launch plan (after bind): out = {element tiles, workgroups of a multi-stage launch that the
+ * plan counts as resident at once, LDS bytes per workgroup, step mode (0 = one launch per
+ * stage, 1 = one launch per step call re-reading tiles every stage, 2 = one launch per step
+ * call with tiles resident in LDS)}.  The count follows from elems_per_block alone, with at
+ * least the LDS that a workgroup takes; a launch per stage (step mode 0) may have more
+ * workgroups than it.  ESDG_ESTATE before bind. */
 esdg_status esdg_swe_launch_info(const esdg_swe *s, int32_t *out4);
 
 /* Message for the last failing call on s (s may be NULL: last failing init on this thread). */

@@ -197,6 +197,7 @@ struct esdg_swe {
   std::map<int, int> epb;          // elements per workgroup per element kind
   size_t lds_bytes = 0;            // dynamic LDS of a workgroup
   size_t limit_bytes = 0;          // the tile limit's count of it (limit_words in device_types.hpp)
+  size_t plan_bytes = 0;           // the same with the default tile shapes: the plan's count
   int block = kBlock;              // stage-kernel workgroup size (kBlockWide if every kind is wide)
   int kind = 0;                    // the one element kind of every instance, else 0
   int tile = 0;                    // its elements per tile
@@ -204,10 +205,10 @@ struct esdg_swe {
                                    // once the residency probe at bind saw the whole grid resident)
   int ref_max = 0;                 // LDS words reserved for the largest reference block
   int max_blocks = 0;              // resident workgroups of the per-stage kernel (set at bind)
-  int multi_blocks = 0;            // and of a multi-stage grid, each workgroup counted with the
-                                   // LDS of the tile limit: the plan of a step call, and what
-                                   // esdg_swe_launch_info reports, follow from the tile sizes
-                                   // and not from how much of that the kernels come to use
+  int multi_blocks = 0;            // and of a multi-stage grid, each workgroup counted with
+                                   // plan_bytes, which is more than the kernels take: the plan of
+                                   // a step call, and what esdg_swe_launch_info reports, stay what
+                                   // they have been for each tile size, whatever the shape
   std::vector<Tile> tiles;
   std::vector<int> tile_begin, tile_count;
   std::vector<InstDesc> desc;
@@ -546,7 +547,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     s->block = all_wide ? kBlockWide : kBlock;
   }
   // elements per workgroup and LDS: the largest reference block + the largest tile
-  size_t tile = 0, limit = 0;
+  size_t tile = 0, limit = 0, plan = 0;
   for (auto &kv : s->refs) {
     const int D = kv.first, N = key_N(D);
     int shape = opt->tile_shape[N] ? opt->tile_shape[N] : default_shape(D, s->fp64);
@@ -564,6 +565,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     s->ref_max = std::max(s->ref_max, ref_words(D));
     tile = std::max(tile, size_t(tile_words(D, E, s->wadg)));
     limit = std::max(limit, size_t(limit_words(D, E, s->wadg, P)));
+    plan = std::max(plan, size_t(limit_words(D, E, s->wadg, s->sbp ? P : shape_parts(default_shape(D, s->fp64)))));
   }
   if (s->kind == 0) s->tile = mixed_tile(s->fp64, s->epb);
   if (s->shapes && (s->contraction != 0 || s->v1)) {
@@ -573,6 +575,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
   }
   s->ref_max = (s->ref_max + 3) & ~3;
   s->limit_bytes = (size_t(s->ref_max) + limit) * s->word;
+  s->plan_bytes = (size_t(s->ref_max) + plan) * s->word;
   if (s->limit_bytes > 160 * 1024) {
     g_init_error = "esdg_swe_init: elems_per_block needs more than 160 KiB of LDS";
     return ESDG_EINVAL;
@@ -667,7 +670,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     hipError_t e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, false, s->lds_bytes,
                                     s->block, &s->max_blocks);
     if (e == hipSuccess)
-      e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, true, s->limit_bytes,
+      e = stage_max_blocks(s->fp64, s->contraction, s->wadg, s->sbp, s->v1, s->kind, s->tile, true, s->plan_bytes,
                            s->block, &s->multi_blocks);
     if (e != hipSuccess) return s->hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (std::getenv("ESDG_SWE_VERBOSE")) {
