@@ -19,6 +19,8 @@ constexpr int kProbeWord = 16;     // int32 word of the flag block counting a re
 // shared by its writer and its pollers alone (packed 32 to a line, the resident launch at
 // N = 1, K = 8192 took 7.1 us a stage instead of 4.9).
 constexpr int kProgressStride = 32;
+// The word of tile t's count, in 64 bits: an ensemble may have more than 2^26 tiles.
+__host__ __device__ constexpr size_t progress_word(int32_t t) { return size_t(uint32_t(t)) * kProgressStride; }
 
 constexpr int kXcds = 8;           // MI355X accelerator complex dies (each with its own L2)
 

@@ -769,7 +769,7 @@ __device__ __forceinline__ bool wait_neighbours(const StageArgs &a, int t, int t
     for (int j = b + int(threadIdx.x); j < e; j += 64) {
       const int u = read_const(a.nbr_idx, j);
       int spins = 0;
-      while (__hip_atomic_load(a.progress + u * kProgressStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+      while (__hip_atomic_load(a.progress + progress_word(u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
         if (++spins > a.spin_limit) { ok = 0; break; }
         __builtin_amdgcn_s_sleep(1);
       }
@@ -787,7 +787,7 @@ __device__ __forceinline__ bool poll_neighbours(const StageArgs &a, int t, int t
     for (int j = b + (int(threadIdx.x) & 63); j < e; j += 64) {
       const int u = read_const(a.nbr_idx, j);
       int spins = 0;
-      while (__hip_atomic_load(a.progress + u * kProgressStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+      while (__hip_atomic_load(a.progress + progress_word(u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
         if (++spins > a.spin_limit) { ok = false; break; }
         __builtin_amdgcn_s_sleep(1);
       }
@@ -805,7 +805,7 @@ __device__ __forceinline__ bool poll_neighbours(const StageArgs &a, int t, int t
 __device__ __forceinline__ void publish(const StageArgs &a, int t, int value) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(a.progress + t * kProgressStride, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) __hip_atomic_store(a.progress + progress_word(t), value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Four values through device-coherent 16-byte loads (the workgroup that stored them may sit on
