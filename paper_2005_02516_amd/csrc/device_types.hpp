@@ -22,6 +22,10 @@ constexpr int kProgressStride = 32;
 // The word of tile t's count, in 64 bits: an ensemble may have more than 2^26 tiles.
 __host__ __device__ constexpr size_t progress_word(int32_t t) { return size_t(uint32_t(t)) * kProgressStride; }
 
+// Workgroups of 256 threads that 256 CUs hold at most (32 waves each): a launch of more tiles is
+// never resident with one tile per workgroup.
+constexpr int kMaxResident = 256 * 8;
+
 constexpr int kXcds = 8;           // MI355X accelerator complex dies (each with its own L2)
 
 // Push-target flag: the face node lies on a reflective wall (Section 2.9); its projection

@@ -192,6 +192,7 @@ struct esdg_swe {
   std::vector<int32_t> nbr_off, nbr_idx;   // tiles holding a face neighbour of each tile (CSR)
   long long stage_count = 0;       // global index of the next stage of a fused launch
   bool fused = false;
+  bool counts = false;             // the workspace holds progress counts
   bool balanced = false;           // mixed degrees: cost-balanced tile ranges uploaded
   size_t ws_bytes = 0;
   std::map<int, int> epb;          // elements per workgroup per element kind
@@ -609,6 +610,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
     }
   }
   s->fused = s->opt.fused_steps != 0;   // mode 2 is resolved at bind, once the resident count is known
+  s->counts = s->opt.fused_steps == 1 || (s->opt.fused_steps == 2 && s->tiles.size() <= size_t(kMaxResident));
   // workspace layout
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -641,7 +643,7 @@ esdg_status esdg_swe_init(int32_t n_inst, const esdg_swe_instance *inst, const e
   s->flag_off = take(256);
   s->partial_off = take(s->tiles.size() * 6 * sizeof(double));
   s->ranges_off = take((s->tiles.size() + 16) * sizeof(int32_t));
-  s->progress_off = take(s->tiles.size() * kProgressStride * sizeof(int32_t));
+  s->progress_off = take(s->counts ? s->tiles.size() * kProgressStride * sizeof(int32_t) : 0);
   s->nbr_off_off = take(s->nbr_off.size() * sizeof(int32_t));
   s->nbr_idx_off = take(std::max<size_t>(s->nbr_idx.size(), 1) * sizeof(int32_t));
   s->ws_bytes = o;
@@ -801,11 +803,9 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
   if ((st = upload(s, s->nbr_off_off, s->nbr_off.data(), s->nbr_off.size() * sizeof(int32_t)))) return st;
   if (!s->nbr_idx.empty() && (st = upload(s, s->nbr_idx_off, s->nbr_idx.data(), s->nbr_idx.size() * sizeof(int32_t))))
     return st;
-  keep.push_back(std::vector<unsigned char>(s->tiles.size() * kProgressStride * sizeof(int32_t), 0));
-  if ((st = upload(s, s->progress_off, keep.back().data(), keep.back().size()))) return st;
   s->stage_count = 0;
   if (s->opt.fused_steps == 2)
-    s->fused = stage_grid(int(s->tiles.size()), s->multi_blocks) >= int(s->tiles.size());
+    s->fused = s->counts && stage_grid(int(s->tiles.size()), s->multi_blocks) >= int(s->tiles.size());
   if (s->fused) {
     int dev = 0, coop = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -813,6 +813,10 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     if (e != hipSuccess) return s->hip_fail(e, "hipDeviceGetAttribute (cooperative launch)");
     if (!coop && s->opt.fused_steps == 2) s->fused = false;   // automatic: fall back to per-stage launches
     else if (!coop) return s->fail(ESDG_EDEVICE, "fused_steps: the device does not support cooperative launches");
+  }
+  if (s->fused) {                  // every tile's count starts at zero
+    keep.push_back(std::vector<unsigned char>(s->tiles.size() * kProgressStride * sizeof(int32_t), 0));
+    if ((st = upload(s, s->progress_off, keep.back().data(), keep.back().size()))) return st;
   }
   // mixed degrees: split the tile list by estimated cost (with a workgroup for every tile there
   // is nothing to split)

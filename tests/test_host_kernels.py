@@ -1,8 +1,15 @@
 """Host-side checks of the kernel sources and of the index and planning helpers that kernels and
 runtime share (CPU; the headers are compiled with g++)."""
+import ctypes as C
 import os
 import re
 import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2005_02516_amd import binding, sbp_rules
+from paper_2005_02516_amd import workloads as wl
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2005_02516_amd", "csrc")
@@ -50,3 +57,34 @@ def test_progress_words_do_not_wrap(tmp_path):
     assert [int(v) for v in out.split()] == [32 * t for t in (0, 1, 2**26 - 1, 2**26, 2**31 - 1)]
     text = open(os.path.join(CSRC, "kernels.hip")).read()
     assert not re.search(r"progress \+ (?!progress_word)", text)
+
+
+def _workspace(w, E, **kw):
+    lib = binding.load_library()
+    scheme = kw.pop("scheme", "modal")
+    xg, yg, b = (np.ascontiguousarray(a) for a in (w.xg, w.yg, w.b_nodes))
+    arr = (binding.esdg_swe_instance * 1)()
+    arr[0] = binding.esdg_swe_instance(w.N, w.K, binding._dptr(xg), binding._dptr(yg), binding._dptr(b), w.Lx, w.Ly)
+    keep = []
+    q = (binding.esdg_swe_quadrature * 1)()
+    q[0] = binding.make_quadrature({"rule": sbp_rules.load(w.N)} if scheme == "sbp" else None, keep)
+    opt = binding.make_options("fp32", "lf", 1.0, True, {w.N: E}, scheme=scheme, **kw)
+    h, nb = C.c_void_p(), C.c_size_t()
+    assert lib.esdg_swe_init(1, arr, q, C.byref(opt), C.byref(h), C.byref(nb)) == binding.ESDG_OK
+    lib.esdg_swe_destroy(h)
+    return nb.value
+
+
+@pytest.mark.parametrize("n", [20, 50])
+def test_progress_counts_only_where_used(n):
+    """The workspace has a 128-byte line per tile for plans that may be one launch per step call
+    (forced, or automatic with at most 2048 tiles), and none for the others."""
+    w = wl.config2(n=n, N=1)
+    tiles = w.K                                    # one element each
+    off, auto, forced = (_workspace(w, 1, fused=f) for f in (False, "auto", True))
+    assert forced - off == 128 * tiles
+    assert auto == (forced if tiles <= 2048 else off)
+    assert _workspace(w, 1, scheme="sbp", fused=True) == _workspace(w, 1, scheme="sbp", fused=False)
+    # DG-SBP: what a tile more costs (tile, descriptors, padding) is less than a line
+    a, b = (_workspace(w, E, scheme="sbp") for E in (1, 2))
+    assert a - b < 128 * (tiles - tiles // 2)
