@@ -18,6 +18,7 @@
 #include "esdg_swe.h"
 #include "device_types.hpp"
 #include "host_setup.hpp"
+#include "tile_plan.hpp"
 
 namespace esdg {
 int mixed_tile(bool fp64, const std::map<int, int> &epb);
@@ -124,45 +125,6 @@ bool shape_valid(int D, bool fp64, int shape) {
   if (P < 1 || P > 4) return false;
   if (R == 1) return true;
   return R == 2 && !fp64 && dim_Nq(D) % 2 == 0 && dim_Nfq(D) % 2 == 0;
-}
-
-// Contiguous tile ranges for G workgroups, range c holding tiles r[c] .. r[c+1]-1 (cum: costs
-// summed up to each tile).  A launch of few tiles per workgroup ends with its most loaded one,
-// so first comes the smallest possible largest range (by bisection; a greedy fill tests a
-// bound), then the ranges lie as near to equal shares as that bound lets them.  (Equal shares
-// alone, each rounded up to a whole tile, overload a workgroup by up to a tile: an ensemble of
-// 45944 elements, N = 2..4, FP32, 66.2 us a stage, 60.6 so; with fewer tiles than workgroups, one
-// each: 6038 elements 15.3 -> 8.5.)
-std::vector<int32_t> split_tiles(const std::vector<long long> &cum, int G) {
-  const int n = int(cum.size()) - 1;
-  auto past = [&](int from, long long cap) {       // end of the longest range from `from` on
-    return int(std::upper_bound(cum.begin() + from, cum.end(), cum[from] + cap) - cum.begin()) - 1;
-  };
-  long long lo = 0, hi = cum[n];                   // ranges of at most hi exist, of at most lo not
-  while (hi - lo > 1) {
-    const long long cap = lo + (hi - lo) / 2;
-    int t = 0;
-    for (int c = 0; c < G && t < n; ++c) {
-      const int e = past(t, cap);
-      if (e == t) break;
-      t = e;
-    }
-    (t == n ? hi : lo) = cap;
-  }
-  // first[c]: the first tile that ranges c .. G-1 can start at and still hold all the rest
-  std::vector<int32_t> first(G + 1, n), r(G + 1, n);
-  for (int c = G - 1; c >= 0; --c) {
-    const auto at = std::lower_bound(cum.begin(), cum.begin() + first[c + 1] + 1, cum[first[c + 1]] - hi);
-    first[c] = int32_t(at - cum.begin());
-  }
-  r[0] = 0;
-  for (int c = 0; c + 1 < G; ++c) {
-    const long long share = (long long)((__int128)cum[n] * (c + 1) / G);
-    int near = int(std::lower_bound(cum.begin(), cum.end(), share) - cum.begin());
-    if (near > 0 && share - cum[near - 1] < cum[near] - share) --near;
-    r[c + 1] = std::min(std::max(near, std::max(first[c + 1], r[c])), past(r[c], hi));
-  }
-  return r;
 }
 
 struct Offsets {
@@ -818,20 +780,14 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     keep.push_back(std::vector<unsigned char>(s->tiles.size() * kProgressStride * sizeof(int32_t), 0));
     if ((st = upload(s, s->progress_off, keep.back().data(), keep.back().size()))) return st;
   }
-  // mixed degrees: split the tile list by estimated cost (with a workgroup for every tile there
-  // is nothing to split)
-  std::vector<int32_t> ranges;
-  {
-    const int G = stage_grid(int(s->tiles.size()), s->fused ? s->multi_blocks : s->max_blocks);
-    if (s->refs.size() > 1 && s->tiles.size() > size_t(G)) {
-      std::vector<long long> cum(s->tiles.size() + 1, 0);
-      for (size_t t = 0; t < s->tiles.size(); ++t)
-        cum[t + 1] = cum[t] + elem_cost(s->host[s->tiles[t].inst].key) * s->tiles[t].ne;
-      ranges = split_tiles(cum, G);
-      if ((st = upload(s, s->ranges_off, ranges.data(), ranges.size() * sizeof(int32_t)))) return st;
-      s->balanced = true;
-    }
-  }
+  // mixed degrees: the tile list split by estimated cost
+  std::vector<long long> cum(1, 0);
+  if (s->refs.size() > 1)
+    for (const Tile &t : s->tiles) cum.push_back(cum.back() + elem_cost(s->host[t.inst].key) * t.ne);
+  const std::vector<int32_t> ranges = tile_ranges(
+      cum, s->refs.size(), stage_grid(int(s->tiles.size()), s->fused ? s->multi_blocks : s->max_blocks));
+  s->balanced = !ranges.empty();
+  if (s->balanced && (st = upload(s, s->ranges_off, ranges.data(), ranges.size() * sizeof(int32_t)))) return st;
   hipError_t e = hipMemsetAsync(s->ws + s->flag_off, 0, 256, s->stream);
   if (e != hipSuccess) return s->hip_fail(e, "hipMemsetAsync (flag)");
   e = hipStreamSynchronize(s->stream);

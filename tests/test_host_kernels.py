@@ -88,3 +88,43 @@ def test_progress_counts_only_where_used(n):
     # DG-SBP: what a tile more costs (tile, descriptors, padding) is less than a line
     a, b = (_workspace(w, E, scheme="sbp") for E in (1, 2))
     assert a - b < 128 * (tiles - tiles // 2)
+
+
+def _smallest_largest(cost, G):
+    """The smallest possible cost of the largest of G contiguous ranges, by dynamic programming."""
+    n = len(cost)
+    best = [sum(cost[:i]) for i in range(n + 1)]           # one range
+    for _ in range(G - 1):
+        best = [min(max(best[j], sum(cost[j:i])) for j in range(i + 1)) for i in range(n + 1)]
+    return best[n]
+
+
+def test_split_tiles(tmp_path):
+    """The ranges cover every tile once, in order, and their largest cost is the smallest possible."""
+    rng = np.random.default_rng(7)
+    cases = [([int(c) for c in rng.integers(1, hi, rng.integers(1, 13))], int(rng.integers(1, 9)))
+             for hi in (2, 4, 60, 600) for _ in range(40)]
+    cases += [([5] * 12, 12), ([1, 1, 1, 100], 3), ([100, 1, 1, 1], 3), ([7], 8)]
+    body = ""
+    for cost, G in cases:
+        cum = np.concatenate([[0], np.cumsum(cost)])
+        body += f"for (int v : split_tiles({{{', '.join(str(c) for c in cum)}}}, {G})) std::printf(\"%d \", v);\n"
+        body += 'std::printf("\\n");\n'
+    rows = _run_cpp(tmp_path, body, ("tile_plan.hpp",)).splitlines()
+    assert len(rows) == len(cases)
+    for (cost, G), row in zip(cases, rows):
+        r = [int(v) for v in row.split()]
+        assert len(r) == G + 1 and r[0] == 0 and r[G] == len(cost) and r == sorted(r), (cost, G, r)
+        assert max(sum(cost[a:b]) for a, b in zip(r, r[1:])) == _smallest_largest(cost, G), (cost, G, r)
+
+
+def test_tile_ranges_only_where_tiles_differ(tmp_path):
+    """No ranges for one kind, nor with a workgroup for every tile; bind takes what a launch uses from
+    this answer, so that a second bind cannot keep ranges its workspace does not hold."""
+    out = _run_cpp(tmp_path, """std::vector<long long> cum = {0, 3, 5, 6, 10};
+std::printf("%d %d %d %d %d", int(tile_ranges(cum, 1, 2).size()), int(tile_ranges(cum, 2, 4).size()),
+            int(tile_ranges(cum, 2, 8).size()), int(tile_ranges(cum, 2, 3).size()), int(tile_ranges({0}, 1, 8).size()));""",
+                   ("tile_plan.hpp",))
+    assert out.split() == ["0", "0", "0", "4", "0"]
+    text = open(os.path.join(CSRC, "runtime.cpp")).read()
+    assert re.findall(r"balanced = ([^;]*);", text) == ["false", "!ranges.empty()"]
