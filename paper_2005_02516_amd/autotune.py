@@ -1,15 +1,15 @@
-"""Autotuner for the tiles of the RK-stage kernel: elements per workgroup E and the
-residual phase's tile shape (R rows per thread, P column parts).
+"""Autotuner for the tiles of the RK-stage kernel: elements per workgroup E.
 
 The stage kernel's LDS footprint, and so its occupancy, grows with the number of elements
-per workgroup E, while small E leaves threads idle in every phase.  The tile shape enters
-the library's limit on E (P) and nothing else: the kernels have one split of the residual
-for each degree.  The best choice depends on the degree N, the precision and how many
-elements there are in total.  ``tune`` times a few LSRK steps for every candidate E with
-the default shape, then every shape the kernel is compiled for at the best few E (HIP
-events on the solver's stream), and records the fastest (E, R, P) in a JSON cache keyed by
-precision, N and a size class of the element count; ``lookup_shapes`` reads it when a
-solver is created without an explicit tile size.
+per workgroup E, while small E leaves threads idle in every phase.  The best choice depends
+on the degree N, the precision and how many elements there are in total.  ``tune`` times a
+few LSRK steps for every candidate E (HIP events on the solver's stream) and records the
+times and the fastest E in a JSON cache keyed by precision, N and a size class of the element
+count; ``lookup_shapes`` reads it when a solver is created without an explicit tile size.
+
+The tile shape (R rows per thread, P column parts) that the library also takes enters its
+limit on E (P) and nothing else: the kernels have one split of the residual for each degree,
+so it is not tuned.  Caches that name one are still read.
 
 Run ``python -m paper_2005_02516_amd.autotune --write`` on the GPU to refresh the cache.
 """
@@ -111,11 +111,10 @@ def lookup(precision: str, sizes: Iterable[Tuple[int, int]]) -> Optional[Dict[in
 
 def lookup_shapes(precision: str, sizes: Iterable[Tuple[int, int]], valu: bool = True):
     """(E per degree, packed tile shape per degree) for instances of (N, K), or (None,
-    None) without cache entries; a degree whose entry has no shape gets the library's
-    default.  The shapes were timed on single-degree workloads with vector-ALU
-    contractions, so a launch of several degrees, the split-bf16 mode or matrix-core
-    contractions (valu False) take the default shape and the best E timed with it; several degrees then have E fitted to the shared
-    LDS (fit_mixed)."""
+    None) without cache entries.  Shapes come only from caches that name one (rows, parts), for
+    launches of one degree; several degrees, the split-bf16 mode and valu False take the E
+    timed fastest with the default shape.
+    Several degrees have E fitted to the shared LDS (fit_mixed)."""
     cache = _load().get("entries", {})
     totals: Dict[int, int] = {}
     for N, K in sizes:
@@ -144,7 +143,8 @@ def lookup_shapes(precision: str, sizes: Iterable[Tuple[int, int]], valu: bool =
 
 
 def time_config(w, precision: str, epb: int, steps: int = 4, warmup: int = 1, shape: Optional[int] = None) -> float:
-    """Milliseconds per RK stage for one workload at tile size epb (and packed tile shape)."""
+    """Milliseconds per RK stage for one workload at tile size epb (and packed tile shape): the
+    least of three runs."""
     import torch
     from .binding import EsdgSwe
     s = EsdgSwe([w], precision=precision, flux=w.flux, g=w.g, elems_per_block=epb, tuned=False, tile_shape=shape)
@@ -154,11 +154,14 @@ def time_config(w, precision: str, epb: int, steps: int = 4, warmup: int = 1, sh
         s.sync()
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
-        e0.record(s.stream)
-        s.step(w.dt, steps)
-        e1.record(s.stream)
-        e1.synchronize()
-        return e0.elapsed_time(e1) / (5 * steps)
+        ms = []
+        for _ in range(3):
+            e0.record(s.stream)
+            s.step(w.dt, steps)
+            e1.record(s.stream)
+            e1.synchronize()
+            ms.append(e0.elapsed_time(e1))
+        return min(ms) / (5 * steps)
     finally:
         s.close()
 
@@ -175,8 +178,8 @@ def lds_ok(N: int, E: int, precision: str, P: Optional[int] = None) -> bool:
 def tune(cases: List[Tuple[int, int]], precisions=("fp32", "fp64"), write: bool = True, log=sys.stderr,
          out: Optional[str] = None, around_cached: bool = False, top: int = 3):
     """around_cached: time only the candidate E within a factor of two of the cached entry's
-    (when there is one), to refresh large classes in less time; top: how many of the best E
-    get every tile shape timed."""
+    (when there is one), to refresh large classes in less time; top: without effect (every
+    tile shape runs the same kernel, so none is timed)."""
     from . import workloads as wl
     data = _load()
     entries = data.setdefault("entries", {})
@@ -184,28 +187,17 @@ def tune(cases: List[Tuple[int, int]], precisions=("fp32", "fp64"), write: bool 
         w = wl.config2(n=n, N=N)
         steps = 4 if w.K < 100000 else 2
         for prec in precisions:
-            # E with the default shape, then every compiled shape at the three best E
             timings = {}
-            R0, P0 = default_shape(N, prec)
-            cached = entries.get(_key(prec, N, w.K), {}).get("epb") if around_cached else None
+            old = entries.get(_key(prec, N, w.K), {})
+            cached = old.get("epb") if around_cached else None
             for E in CANDIDATES:
-                if not lds_ok(N, E, prec, P0) or (cached and not cached / 2 <= E <= cached * 2):
+                if not lds_ok(N, E, prec) or (cached and not cached / 2 <= E <= cached * 2):
                     continue
-                timings[E] = time_config(w, prec, E, steps=steps, shape=shape_code(R0, P0))
+                timings[E] = time_config(w, prec, E, steps=steps)
                 print(f"# tune {prec} N={N} K={w.K} E={E}: {timings[E] * 1e3:.1f} us/stage", file=log, flush=True)
-            shaped = {(E, R0, P0): timings[E] for E in timings}
-            for E in sorted(timings, key=timings.get)[:top]:
-                for R, P in shapes(N, prec):
-                    if (E, R, P) in shaped or not lds_ok(N, E, prec, P):
-                        continue
-                    shaped[(E, R, P)] = time_config(w, prec, E, steps=steps, shape=shape_code(R, P))
-                    print(f"# tune {prec} N={N} K={w.K} E={E} R={R} P={P}: {shaped[(E, R, P)] * 1e3:.1f} us/stage",
-                          file=log, flush=True)
-            E, R, P = min(shaped, key=shaped.get)
             entries[_key(prec, N, w.K)] = {
-                "epb": E, "rows": R, "parts": P, "K": w.K,
-                "us_per_stage": {str(k): round(v * 1e3, 2) for k, v in timings.items()},
-                "shape_us_per_stage": {f"{e}:{r}:{p}": round(v * 1e3, 2) for (e, r, p), v in shaped.items()}}
+                "epb": min(timings, key=timings.get), "K": w.K,
+                "us_per_stage": {str(k): round(v * 1e3, 2) for k, v in timings.items()}}
     data["device"] = "gfx950 (MI355X)"
     data["note"] = "written by `python -m paper_2005_02516_amd.autotune --write` on the GPU"
     if write:
@@ -239,7 +231,7 @@ if __name__ == "__main__":
                     help="comma-separated N:n (degree, squares per side of the config-2 mesh); default: all")
     ap.add_argument("--around-cached", action="store_true",
                     help="time only E within a factor of two of the cached entry's")
-    ap.add_argument("--top", type=int, default=3, help="E values whose tile shapes are all timed")
+    ap.add_argument("--top", type=int, default=3, help="without effect (tile shapes are not timed)")
     args = ap.parse_args()
     tune(parse_cases(args.cases), precisions=tuple(args.precisions.split(",")), write=args.write, out=args.out,
          around_cached=args.around_cached, top=args.top)
