@@ -109,13 +109,29 @@ def lookup(precision: str, sizes: Iterable[Tuple[int, int]]) -> Optional[Dict[in
     return lookup_shapes(precision, sizes)[0]
 
 
-def lookup_shapes(precision: str, sizes: Iterable[Tuple[int, int]], valu: bool = True):
+def best_by_rounds(table: Dict[str, List[float]], Ks: Iterable[int]) -> int:
+    """The E of least time for meshes of Ks elements, from {E: [workgroups resident on 256 CUs,
+    us of a round of them, us of a stage whose tiles are all resident]}: a stage takes whole
+    rounds, so between two sizes the rounds that a mesh needs decide."""
+    Ks = list(Ks)
+
+    def us(E):
+        blocks, each, resident = table[E]
+        rounds = -(-sum(-(-K // int(E)) for K in Ks) // int(blocks))
+        return resident if rounds == 1 else rounds * each
+    return int(min(table, key=us))
+
+
+def lookup_shapes(precision: str, sizes: Iterable[Tuple[int, int]], valu: bool = True, mass: str = "stored"):
     """(E per degree, packed tile shape per degree) for instances of (N, K), or (None,
     None) without cache entries.  Shapes come only from caches that name one (rows, parts), for
     launches of one degree; several degrees, the split-bf16 mode and valu False take the E
-    timed fastest with the default shape.
+    timed fastest with the default shape.  An entry with a rounds table for the precision has E
+    taken from it (best_by_rounds) for one degree and the stored mass inverse, whose LDS
+    the table's workgroups are counted with; other launches take its epb_else where it has one.
     Several degrees have E fitted to the shared LDS (fit_mixed)."""
     cache = _load().get("entries", {})
+    sizes = list(sizes)
     totals: Dict[int, int] = {}
     for N, K in sizes:
         totals[N] = totals.get(N, 0) + K
@@ -128,14 +144,19 @@ def lookup_shapes(precision: str, sizes: Iterable[Tuple[int, int]], valu: bool =
             e = next((cache[f"{prec}:N{N}:{cls}"] for cls in order[size_class(K)]
                       if f"{prec}:N{N}:{cls}" in cache), None)
             if e:
-                if "rows" in e and own_shape:
+                table = e.get("rounds", {}).get(precision)
+                if table and len(totals) == 1 and mass == "stored":
+                    out[N] = best_by_rounds(table, [K for _, K in sizes])
+                elif "rows" in e and own_shape:
                     out[N] = int(e["epb"])
                     shp[N] = shape_code(int(e["rows"]), int(e["parts"]))
                 elif "rows" in e:           # the fastest E with the default shape
                     t = e["us_per_stage"]
                     out[N] = int(min(t, key=lambda E: t[E]))
-                else:
+                elif len(totals) == 1 and mass == "stored":
                     out[N] = int(e["epb"])
+                else:
+                    out[N] = int(e.get("epb_else", e["epb"]))
                 break
     if not out:
         return None, None
@@ -179,7 +200,8 @@ def tune(cases: List[Tuple[int, int]], precisions=("fp32", "fp64"), write: bool 
          out: Optional[str] = None, around_cached: bool = False, top: int = 3):
     """around_cached: time only the candidate E within a factor of two of the cached entry's
     (when there is one), to refresh large classes in less time; top: without effect (every
-    tile shape runs the same kernel, so none is timed)."""
+    tile shape runs the same kernel, so none is timed).  What an entry says about other launches
+    (rounds, epb_else) is kept."""
     from . import workloads as wl
     data = _load()
     entries = data.setdefault("entries", {})
@@ -197,7 +219,8 @@ def tune(cases: List[Tuple[int, int]], precisions=("fp32", "fp64"), write: bool 
                 print(f"# tune {prec} N={N} K={w.K} E={E}: {timings[E] * 1e3:.1f} us/stage", file=log, flush=True)
             entries[_key(prec, N, w.K)] = {
                 "epb": min(timings, key=timings.get), "K": w.K,
-                "us_per_stage": {str(k): round(v * 1e3, 2) for k, v in timings.items()}}
+                "us_per_stage": {str(k): round(v * 1e3, 2) for k, v in timings.items()},
+                **{k: old[k] for k in ("rounds", "epb_else") if k in old}}
     data["device"] = "gfx950 (MI355X)"
     data["note"] = "written by `python -m paper_2005_02516_amd.autotune --write` on the GPU"
     if write:

@@ -182,7 +182,7 @@ class EsdgSwe:
         if not elems_per_block and tuned and default_rules:   # the tuning cache covers the default rules
             from .autotune import lookup_shapes
             elems_per_block, tuned_shape = lookup_shapes(precision, [(w.N, w.K) for w in instances],
-                                                         valu=not matrix_cores)
+                                                         valu=not matrix_cores, mass=mass)
             if tile_shape is None:
                 tile_shape = tuned_shape
         if fused is None:       # one launch per step call when tiles can stay resident
