@@ -389,7 +389,7 @@ def main():
                     help="inverse curved mass matrices: stored per element (default), or the "
                          "weight-adjusted inverse (w/J per volume node)")
     ap.add_argument("--matrix-cores", action="store_true",
-                    help="projection/lift contractions on the matrix cores in the bulk precision")
+                    help="accepted, without effect: the contractions always run on the matrix cores")
     ap.add_argument("--ensemble", type=int, default=0,
                     help="time the batched ensemble of this many instances instead (256 = the full ensemble)")
     ap.add_argument("--copy-probe", action="store_true",
@@ -508,10 +508,11 @@ def main():
                    "K": w.K, "N": w.N, "DOF": dof, "precision": prec,
                    "hip_graph": (not args.no_graph) and plans[prec]["step_mode"] == 0,
                    "elements_per_workgroup": epb_used.get(prec, 0),
-                   "matrix_cores": bool(args.matrix_cores or prec == "bf16x3"),
+                   "matrix_cores": True,      # every contraction with a constant operator
                    "mass_inverse": {"stored": "stored per element", "wadg": "weight-adjusted"}[args.mass],
                    "launch": STEP_MODES[plans[prec]["step_mode"]],
-                   "workgroups": plans[prec]["resident_workgroups"], "tiles": plans[prec]["tiles"]},
+                   # of a multi-stage launch, as the plan counts them
+                   "resident_workgroups": plans[prec]["resident_workgroups"], "tiles": plans[prec]["tiles"]},
         "roofline": roof,
     }
     if "fp64" in results and prec != "fp64":

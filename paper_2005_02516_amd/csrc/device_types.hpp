@@ -118,7 +118,7 @@ __host__ __device__ constexpr int make_shape(int R, int P) { return (R << 4) | P
 
 // Kinds with many hybrid nodes (N=5, and N=4 with N+2 points): their reference block fills
 // a quarter of a CU's LDS, so their launches run workgroups of kBlockWide threads (twice the
-// elements sharing one copy of it), and their residual rows use balanced column chunks.
+// elements sharing one copy of it), and their residual rows have a split of their own.
 __host__ __device__ constexpr bool wide_kind(int D) { return !key_sbp(D) && dim_Nh(D) >= 50; }
 
 // Reals per element of the block that holds the fetched u~ [4][Nh] (dead after the node
@@ -137,7 +137,10 @@ __host__ __device__ constexpr int tile_words(int D, int E, bool wadg = false) {
 }
 
 // The tile size limit of the ABI: E elements with P column parts are accepted if this many
-// words and the reference block fit 160 KiB.  tile_words is below it for every kind.
+// words and the reference block fit 160 KiB.  tile_words is below it for every kind.  With the
+// default shape's P it is also what the launch plan counts a workgroup of a multi-stage launch
+// with, so that a tile size has the plan it always had; FP32 N = 3, E = 8: 33.4 KB against the
+// 29.9 KB taken, four workgroups a CU.
 __host__ __device__ constexpr int limit_words(int D, int E, bool wadg, int P) {
   const int rec = 12 * dim_Nh(D) + (dim_Nh(D) % 2 == 0 ? 4 : 0), parts = 3 * P * dim_Nh(D) + 3 * dim_Np(D);
   const int raw = key_sbp(D) ? 6 * dim_Nh(D) : parts > 8 * dim_Nh(D) ? parts : 8 * dim_Nh(D);
@@ -197,8 +200,8 @@ struct StageArgs {
   int32_t ntiles;
   int32_t mode;
   int32_t ref_words_max;  // LDS words reserved for the reference block (largest degree)
-  int32_t contraction;    // constant-matrix contractions: 0 VALU, 1 matrix cores in the bulk
-                          // precision, 2 matrix cores with split-bf16 products
+  int32_t contraction;    // constant-matrix contractions, on the matrix cores: 2 with split-bf16
+                          // products, else in the bulk precision
   int32_t wadg;           // 0: stored inverse mass matrices; 1: weight-adjusted inverse
   int32_t v1;             // an instance is of a variant-1 kind (selects the stage-kernel build)
   int32_t kind;           // the element kind of every instance of a single-kind launch, which
@@ -224,7 +227,7 @@ struct StageArgs {
   int32_t stage0, nstages;
   int32_t spin_limit;     // polls of one neighbour count before the wait gives up
   int32_t resident;       // multi-stage launch with at most one tile per workgroup: the tile
-                          // stays in LDS from its first stage to its last (see stage_tile)
+                          // stays in LDS from its first stage to its last (see resident_tile)
   double rk_a5[5], rk_b5[5];
 };
 

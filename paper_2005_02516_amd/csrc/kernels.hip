@@ -86,8 +86,8 @@ struct FieldTask {
 // l/16][col l%16]; it receives D[row 4(l/16) + r][col l%16], r = 0..3, from the f32 and
 // bf16 instructions, but D[row l/16 + 4r][col l%16] from v_mfma_f64_16x16x4_f64.
 // Out-of-range rows, columns and k are zero.  Modes:
-//   kMfmaNative: v_mfma_f32_16x16x4_f32 or v_mfma_f64_16x16x4_f64 (same rounding as the
-//                VALU path up to summation order);
+//   kMfmaNative: v_mfma_f32_16x16x4_f32 or v_mfma_f64_16x16x4_f64 (products and sums in the
+//                bulk precision);
 //   kMfmaBf16x3: each operand split x = hi + lo (hi = bf16(x), lo = bf16(x - hi)), product
 //                hi_a hi_b + hi_a lo_b + lo_a hi_b by v_mfma_f32_16x16x16_bf16 with float
 //                accumulation (relative error ~2^-16 per product).
@@ -836,8 +836,9 @@ __device__ __forceinline__ auto fetched_neighbours(const LT &L) {
 
 // First of the interface tasks of this thread: in the modal kinds from the last wave on, since
 // the pair loop gives its longer tasks (volume rows) to the first waves (FP32 N = 3, K = 20402
-// 29.5 -> 28.8 us a stage, N = 1, K = 65522 23.4 -> 22.9).  The wide kinds' last waves have the
-// longer ones, and in DG-SBP at N = 3 the third wave has both sorts (K = 32768 34.3 us; 35.8
+// 29.5 -> 28.8 us a stage, N = 1, K = 65522 23.4 -> 22.9).  FP64 N = 3, one launch per stage, pays
+// (K = 8192 20.65 -> 21.2); without the reversal there it stays at 21.2, and the other FP64 kinds
+// lose.  The wide kinds' last waves have the longer ones, and in DG-SBP at N = 3 the third wave has both sorts (K = 32768 34.3 us; 35.8
 // from the last wave on).
 template <int N, class LT>
 __device__ __forceinline__ int interface_tid() {
@@ -1056,9 +1057,10 @@ __host__ __device__ constexpr int stage_kernel_threads(int kind, int tile) {
 // sizes leaves room for, except in the builds with run-time offsets: those also serve small tiles,
 // of which more fit a CU (five workgroups where registers and LDS meet, six in FP32 at N = 4,
 // and three of 512 threads at N = 5).  Left at four they took up to 101 registers, so that fewer
-// workgroups than tiles were resident: FP32 N = 3, K = 4608, four elements to a tile 8.5 -> 11.6 us
-// a stage, FP64 N = 2, four 9.8 -> 18.6, FP32 N = 5, two 37.6 -> 49.0.  FP64 N = 4 and 5 have no
-// room in LDS for a fifth (a third at N = 5).
+// workgroups than tiles were resident, K = 4608: FP32 N = 3, four elements to a tile 11.6 us a
+// stage instead of 6.3, FP64 N = 2, four 18.6 instead of 7.4, FP32 N = 5, two 49.0 instead of 35.6.
+// FP32 N = 4 is slower at six where LDS holds fewer: eight elements, K = 512 9.1 -> 10.4.  FP64
+// N = 4 and 5 have no room in LDS for a fifth (a third at N = 5).
 template <typename real> __host__ __device__ constexpr int stage_waves(int kind, int tile) {
   if (kind == 0 || key_variant(kind) != 0 || tile != 0) return 4;
   return kind <= 3 ? 5 : sizeof(real) == 4 ? 6 : 4;
@@ -1082,8 +1084,8 @@ stage_kernel(StageArgs a) {
   // MULTI: the multi-stage instantiation; the per-stage one compiles without the waits,
   // resident tiles and device-coherent pushes (and keeps the registers they would cost)
   const bool multi = MULTI && a.progress != nullptr;
-  // resident: the launch gives this workgroup at most one tile (cost-balanced ranges can
-  // still give a workgroup two; that one then re-reads its tiles every stage)
+  // resident: the launch has a workgroup for every tile (and then no ranges), so this one has at
+  // most one
   const bool resident = multi && a.resident && t1 - t0 <= 1;
   const int nst = !multi ? 1 : resident ? (t1 > t0 ? 1 : 0) : a.nstages;
   int loaded_N = 0;

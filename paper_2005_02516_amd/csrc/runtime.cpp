@@ -138,7 +138,7 @@ struct esdg_swe {
   esdg_swe_options opt{};
   bool fp64 = true;
   bool bf16x3 = false;
-  int contraction = 0;             // 0 VALU, 1 matrix cores (bulk precision), 2 split-bf16
+  int contraction = 0;             // 2: split-bf16 contractions, else in the bulk precision
   bool wadg = false;               // weight-adjusted mass inverse instead of stored inverses
   bool sbp = false;                // DG-SBP scheme (every instance)
   bool v1 = false;                 // some instance is of a variant-1 kind (N+2 points)
@@ -639,8 +639,7 @@ esdg_status esdg_swe_bind(esdg_swe *s, void *dev_workspace, size_t bytes, void *
     if (e != hipSuccess) return s->hip_fail(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     if (std::getenv("ESDG_SWE_VERBOSE")) {
       std::fprintf(stderr, "esdg_swe: %s, %d threads and LDS %zu B per workgroup, %d resident workgroups, %zu tiles;",
-                   s->fp64 ? (s->contraction ? "fp64+mfma" : "fp64")
-                           : (s->bf16x3 ? "fp32+bf16x3" : (s->contraction ? "fp32+mfma" : "fp32")), s->block, s->lds_bytes,
+                   s->fp64 ? "fp64" : (s->bf16x3 ? "fp32+bf16x3" : "fp32"), s->block, s->lds_bytes,
                    s->max_blocks, s->tiles.size());
       for (auto &kv : s->epb)
         std::fprintf(stderr, " N=%d%s: %d elements/tile", key_N(kv.first),
@@ -955,7 +954,7 @@ static esdg_status run_steps_direct(esdg_swe *s, int nsteps) {
   return ESDG_OK;
 }
 
-// All 5 * nsteps stages in one cooperative launch (see stage_kernel).  Stage counts are
+// All 5 * nsteps stages in one multi-stage launch (see stage_kernel).  Stage counts are
 // global and monotone; launches of at most 2^20 steps keep them well inside int32.
 static esdg_status run_steps_fused(esdg_swe *s, int nsteps) {
   for (int done = 0; done < nsteps;) {
@@ -984,7 +983,7 @@ static esdg_status run_steps_fused(esdg_swe *s, int nsteps) {
       a.rk_b5[st] = kRkB[st];
     }
     hipError_t e = launch_stage_fused(s->fp64, a, s->multi_blocks, s->lds_bytes, s->block, s->cooperative, s->stream);
-    if (e != hipSuccess) return s->hip_fail(e, "hipLaunchCooperativeKernel (fused steps)");
+    if (e != hipSuccess) return s->hip_fail(e, "multi-stage launch");
     s->stage_count += 5LL * n;
     if (n & 1) s->parity = 1 - s->parity;
     done += n;

@@ -14,7 +14,7 @@ namespace esdg {
 // bound), then the ranges lie as near to equal shares as that bound lets them.  (Equal shares
 // alone, each rounded up to a whole tile, overload a workgroup by up to a tile: an ensemble of
 // 45944 elements, N = 2..4, FP32, 66.2 us a stage, 60.6 so; with fewer tiles than workgroups, one
-// each: 6038 elements 15.3 -> 8.5.)
+// each: 6038 elements 15.3 -> 8.5.  Of the ensembles timed one lost: 18198 elements 29.2 -> 30.9.)
 inline std::vector<int32_t> split_tiles(const std::vector<long long> &cum, int G) {
   const int n = int(cum.size()) - 1;
   auto past = [&](int from, long long cap) {       // end of the longest range from `from` on
