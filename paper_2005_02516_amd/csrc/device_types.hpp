@@ -139,8 +139,8 @@ __host__ __device__ constexpr int tile_words(int D, int E, bool wadg = false) {
 // The tile size limit of the ABI: E elements with P column parts are accepted if this many
 // words and the reference block fit 160 KiB.  tile_words is below it for every kind.  With the
 // default shape's P it is also what the launch plan counts a workgroup of a multi-stage launch
-// with, so that a tile size has the plan it always had; FP32 N = 3, E = 8: 33.4 KB against the
-// 29.9 KB taken, four workgroups a CU.
+// with, so that a tile size has the plan it always had; FP32 N = 3, E = 8: 32.6 KiB against the
+// 29.9 KiB taken, four workgroups a CU.
 __host__ __device__ constexpr int limit_words(int D, int E, bool wadg, int P) {
   const int rec = 12 * dim_Nh(D) + (dim_Nh(D) % 2 == 0 ? 4 : 0), parts = 3 * P * dim_Nh(D) + 3 * dim_Np(D);
   const int raw = key_sbp(D) ? 6 * dim_Nh(D) : parts > 8 * dim_Nh(D) ? parts : 8 * dim_Nh(D);
